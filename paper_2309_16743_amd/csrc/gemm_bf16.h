@@ -246,8 +246,24 @@ struct BEpi {
     constexpr int NG = NP / G;
     static_assert(NP % G == 0, "pass groups");
     float* const P = reinterpret_cast<float*>(g.C);
-    if (!cfull || col >= g.N) {
-      stage();
+    const AdamArgs ad = g.adam.resolved();
+    f32x4 pp[2][G], mm[2][G], vv[2][G];
+    auto load = [&](int grp, int buf) {
+#pragma unroll
+      for (int u = 0; u < G; ++u) {
+        const int64_t m = min(m0 + rl + RPP * (grp * G + u), g.M - 1);   // clamped rows are not stored
+        const int64_t o = m * g.ldc + col;
+        pp[buf][u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(P + o));
+        mm[buf][u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(g.adam_m + o));
+        vv[buf][u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(g.adam_v + o));
+      }
+    };
+    // stage() holds barriers and each lane reads values that other lanes of its
+    // wavefront stage, so all lanes call it together: also in a wavefront whose
+    // columns cross N (N not a multiple of 4 splits one of its column groups)
+    if (cfull) load(0, 0);
+    stage();
+    if (!cfull) {
       if (col >= g.N) return;
       for (int i = 0; i < NP; ++i) {
         const int rr = rl + RPP * i;
@@ -266,20 +282,6 @@ struct BEpi {
       }
       return;
     }
-    const AdamArgs ad = g.adam.resolved();
-    f32x4 pp[2][G], mm[2][G], vv[2][G];
-    auto load = [&](int grp, int buf) {
-#pragma unroll
-      for (int u = 0; u < G; ++u) {
-        const int64_t m = min(m0 + rl + RPP * (grp * G + u), g.M - 1);   // clamped rows are not stored
-        const int64_t o = m * g.ldc + col;
-        pp[buf][u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(P + o));
-        mm[buf][u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(g.adam_m + o));
-        vv[buf][u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(g.adam_v + o));
-      }
-    };
-    load(0, 0);
-    stage();
 #pragma unroll
     for (int gi = 0; gi < NG; ++gi) {
       const int buf = gi & 1;

@@ -73,6 +73,8 @@ SHAPES = [
     ((6, 2048, 2048, 2048, 4096), 1024),   # the deep 1000x1000 net's hidden widths and batch
     ((6, 16, 16, 1), 1),               # one sample, one output
     ((6, 40, 24, 9), 3),               # three samples, ragged narrow widths
+    ((6, 64, 83, 500), 36),            # fused update whose last column group is partial and starts a 16-column fragment
+    ((6, 64, 470, 30001), 64),         # the same on the pipelined kernel's tiles
 ]
 
 

@@ -61,6 +61,8 @@ struct GemmArgs {
   int64_t ldmask;
   float* rowsum;            // optional: sum_k A(m, k) for m of the block's rows (n tile 0 only)
   int64_t rowsum_stride;    // SplitK: elements between consecutive split slices of rowsum
+  bool padded_a, padded_b;  // rows of an MNMajor operand are allocated up to a multiple of 8 values, zero past
+                            // the operand (read by gemm_f32x3_kernel only)
   float* adam_m;            // Adam: moments at C's offsets
   float* adam_v;
   AdamArgs adam;

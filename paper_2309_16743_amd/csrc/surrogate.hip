@@ -18,6 +18,7 @@
 #include "common.h"
 #include "gemm_bf16.h"
 #include "gemm_f32.h"
+#include "gemm_f32x3.h"
 #include "hidden_small.h"
 #include "philox.h"
 #include "surrogate.h"
@@ -46,6 +47,12 @@ __global__ void init_layer_kernel(float* __restrict__ W, float* __restrict__ b, 
 __global__ void fill_kernel(float* __restrict__ p, int64_t n, float v) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
+}
+
+// p[m][w .. ld) = 0 for `rows` rows of leading dimension ld.
+__global__ void zero_pad_kernel(float* __restrict__ p, int64_t ld, int64_t w, int64_t rows) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, pad = ld - w;
+  if (i < rows * pad) p[i / pad * ld + w + i % pad] = 0.f;
 }
 
 // First layer with a small input width K (the 6 inputs (X, t)):
@@ -417,6 +424,62 @@ __global__ void splitk_epilogue_bf16_kernel(const float* __restrict__ ws, int64_
   }
 }
 
+// Split-K epilogue for many splits: out[m][n] = epi(sum_s ws[s][m][n]) with epi
+// as in splitk_epilogue_kernel (Out float) or splitk_epilogue_bf16_kernel (Out
+// uint16_t, bf16 mask).  16 threads of a block share a group of 4 columns:
+// thread q sums splits q, q + 16, ... and the 16 sums are added in order, so
+// that a narrow result (10 x 256 with 512 splits, 368 x 109 with 170) has 16
+// times the loads in flight: 30 -> 8 us and 51 -> 8 us.  Results of 65,536
+// groups or more fill the chip with one thread per group (32 splits of 1024 x
+// 256: 9.3 us against 10.3 us here; 16 of 1024 x 2048: 13 against 56 us).
+constexpr int kWideSplits = 16;
+inline bool splitk_wide(int64_t splits, int64_t groups) { return splits >= kWideSplits && groups < 65536; }
+template <class Out>
+__global__ __launch_bounds__(256) void splitk_wide_kernel(const float* __restrict__ ws, int64_t splits,
+                                                          int64_t split_stride, int64_t M, int64_t N, int64_t ldws,
+                                                          const float* __restrict__ bias, int relu,
+                                                          const Out* __restrict__ mask, int64_t ldm,
+                                                          Out* __restrict__ out, int64_t ldo) {
+  __shared__ f32x4 part[kWideSplits][16];
+  const int c = threadIdx.x % 16, q = threadIdx.x / 16;
+  const int64_t groups = (N + 3) / 4;
+  const int64_t t = (int64_t)blockIdx.x * 16 + c;
+  const int64_t m = t / groups, n = (t % groups) * 4;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  if (m < M) {
+    // ldws is a multiple of 4: a partial group reads padding, which is dropped below
+    const f32x4* src = reinterpret_cast<const f32x4*>(ws + m * ldws + n);
+    const int64_t st4 = split_stride / 4;
+    int64_t p = q;
+    for (; p + 3 * kWideSplits < splits; p += 4 * kWideSplits) {
+      f32x4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = src[(p + u * kWideSplits) * st4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc += v[u];
+    }
+    for (; p < splits; p += kWideSplits) acc += src[p * st4];
+  }
+  part[q][c] = acc;
+  __syncthreads();
+  if (q != 0 || m >= M) return;
+#pragma unroll
+  for (int u = 1; u < kWideSplits; ++u) acc += part[u][c];
+  const int cnt = (int)min((int64_t)4, N - n);
+  for (int e = 0; e < cnt; ++e) {
+    float x = acc[e];
+    if (bias) x += bias[n + e];
+    if (relu) x = x > 0.f ? x : 0.f;
+    if constexpr (sizeof(Out) == 2) {
+      if (mask) x = bf2f(mask[m * ldm + n + e]) > 0.f ? x : 0.f;
+      out[m * ldo + n + e] = f2bf(x);
+    } else {
+      if (mask) x = mask[m * ldm + n + e] > 0.f ? x : 0.f;
+      out[m * ldo + n + e] = x;
+    }
+  }
+}
+
 }  // namespace ot
 
 // ===================================================================== host side
@@ -544,10 +607,11 @@ int refuse_alloc(const char* what) {
   return ot::set_error(OT_E_STATE, "%s would allocate inside surrogate_predict_noalloc", what);
 }
 
-int ensure_workspace(ot_surrogate* s, int64_t rows) {
+// creating: the caller synchronises the device before the workspace is used.
+int ensure_workspace(ot_surrogate* s, int64_t rows, bool creating = false) {
   if (rows <= s->ws_rows) return OT_OK;
   if (s->no_alloc) return refuse_alloc("the batch workspace");
-  OT_HIP(hipDeviceSynchronize());
+  if (!creating) OT_HIP(hipDeviceSynchronize());
   free_workspace(s);
   const int L = s->L;
   int rc;
@@ -557,10 +621,24 @@ int ensure_workspace(ot_surrogate* s, int64_t rows) {
     for (int l = 1; l <= L; ++l)
       if ((rc = salloc((void**)&s->dz16[l], (size_t)rows * s->ld[l] * sizeof(uint16_t)))) return rc;
   } else {
+    // rows are padded to a multiple of 8 values, which the weight gradient may
+    // read (into results it drops): the padding is zero
+    bool cleared = false;
+    auto with_zero_pad = [&](float** p, int l) -> int {
+      int rc = salloc((void**)p, (size_t)rows * s->ld[l] * sizeof(float));
+      const int64_t pad = s->ld[l] - s->widths[l];
+      if (rc || pad == 0) return rc;
+      hipLaunchKernelGGL(ot::zero_pad_kernel, dim3((unsigned)ot::ceil_div(rows * pad, 256)), dim3(256), 0, 0, *p,
+                         s->ld[l], s->widths[l], rows);
+      OT_LAUNCHED("zero_pad_kernel");
+      cleared = true;
+      return OT_OK;
+    };
     for (int l = 1; l < L; ++l)
-      if ((rc = salloc((void**)&s->act[l], (size_t)rows * s->ld[l] * sizeof(float)))) return rc;
+      if ((rc = with_zero_pad(&s->act[l], l))) return rc;
     for (int l = 1; l <= L; ++l)
-      if ((rc = salloc((void**)&s->dz[l], (size_t)rows * s->ld[l] * sizeof(float)))) return rc;
+      if ((rc = with_zero_pad(&s->dz[l], l))) return rc;
+    if (cleared && !creating) OT_HIP(hipStreamSynchronize(0));
   }
   // one loss partial per block of the output GEMM (64 x 64 tiles bound the count)
   s->n_partials_cap = ot::ceil_div(rows, 64) * ot::ceil_div(s->widths[L], 64) + 64;
@@ -578,13 +656,19 @@ int ensure_workspace(ot_surrogate* s, int64_t rows) {
   return OT_OK;
 }
 
-// Tile shapes (4 wavefronts each): 128 x 128, 64 x 128, 64 x 64.
-enum Cfg : int { kC128x128 = 0, kC64x128 = 1, kC64x64 = 2 };
+// Tile shapes (4 wavefronts each): 128 x 128, 64 x 128, 64 x 64 on fp32 MFMAs;
+// 128 x 128, 64 x 128, 64 x 64, 32 x 256 and 64 x 256 on three bf16 terms
+// (gemm_f32x3.h).
+enum Cfg : int { kC128x128 = 0, kC64x128 = 1, kC64x64 = 2, kX128 = 3, kX64 = 4, kX32W = 5, kX64W = 6, kX64x128 = 7 };
 
 int64_t tiles_of(int cfg, int64_t M, int64_t N) {
   switch (cfg) {
     case kC128x128: return ot::gemm_tiles<2, 2, 4, 4>(M, N);
     case kC64x128: return ot::gemm_tiles<2, 2, 2, 4>(M, N);
+    case kX128: return ot::ceil_div(M, 128) * ot::ceil_div(N, 128);
+    case kX64x128: return ot::ceil_div(M, 64) * ot::ceil_div(N, 128);
+    case kX32W: return ot::ceil_div(M, 32) * ot::ceil_div(N, 256);
+    case kX64W: return ot::ceil_div(M, 64) * ot::ceil_div(N, 256);
     default: return ot::gemm_tiles<2, 2, 2, 2>(M, N);
   }
 }
@@ -596,6 +680,38 @@ struct Plan {
   int64_t blocks = 0;
 };
 
+// The plan on three bf16 terms, or false where the fp32 MFMA kernel is as good:
+// below 4e8 flops launch and fill time dominate (49 x 15766 x 242: forward 18
+// against 20 us, gradients even or slower), a weight gradient over fewer than 128 rows is bound by its
+// Adam epilogue (1000000 x 256 over 10 rows: 1146 us on fp32 MFMAs, 1168 here),
+// and fewer than 192 blocks leave CUs idle.  Forward products are never split
+// here (their partials would need scratch that surrogate_predict_noalloc's
+// callers did not have to fit); 64 x 128 tiles when they give two blocks per CU
+// (1024 x 10000 x 256: 54 us, 61 on 64 x 64 tiles), else 64 x 64 (331 x 6561 x 437:
+// 32 us, 35 on 64 x 128).  Backward products are split until about 512 blocks
+// (two 128 x 128 blocks share a CU; more would queue behind them: 10000 x 256
+// over 1024 rows in 3 splits 39 us, in 4 47 us).
+bool make_plan_x3(int64_t M, int64_t N, int64_t K, bool backward, Plan* p) {
+  constexpr int64_t kCUs = 256;
+  if (2.0 * M * N * K < 4e8) return false;
+  const int wide = M <= 32 ? kX32W : kX64W;
+  if (!backward) {
+    if (M <= 64 && tiles_of(wide, M, N) >= kCUs) p->cfg = wide;
+    else p->cfg = tiles_of(kX64x128, M, N) >= 2 * kCUs ? kX64x128 : kX64;
+    if (tiles_of(p->cfg, M, N) < kCUs - 64) return false;
+    p->splits = 1;
+  } else {
+    p->cfg = (M <= 64 && N > 128) ? wide : (M <= 64 || N <= 64) ? kX64 : kX128;
+    const int64_t t = tiles_of(p->cfg, M, N);
+    p->splits = std::max<int64_t>(1, std::min<int64_t>(2 * kCUs / t, K / 128));
+    if (t * p->splits < kCUs - 64 || K < 128) return false;
+  }
+  p->k_chunk = ot::round_up(ot::ceil_div(K, p->splits), 16);
+  p->splits = std::max<int64_t>(1, ot::ceil_div(K, p->k_chunk));
+  p->blocks = tiles_of(p->cfg, M, N) * p->splits;
+  return true;
+}
+
 // Tile and k-split choice (measured on MI355X at the surrogate's shapes).
 // Whole tiles per CU matter more than tile size: a launch whose block count
 // leaves some CUs a block more than others loses that fraction, so the plan
@@ -604,9 +720,11 @@ struct Plan {
 // tiles (>= 256 deep per split), and splits short problems down to 32-deep
 // ranges until every CU has a block.  The MSE epilogue needs whole sums and
 // is never split.
-Plan make_plan(int64_t M, int64_t N, int64_t K, bool allow_split) {
+Plan make_plan(int64_t M, int64_t N, int64_t K, bool allow_split, bool backward = false) {
   constexpr int64_t kCUs = 256;
   Plan p;
+  if (make_plan_x3(M, N, K, backward, &p)) return p;
+  p = Plan{};
   if (tiles_of(kC64x128, M, N) >= 960 || !allow_split) {
     p.cfg = kC64x128;
     if (tiles_of(kC64x128, M, N) < kCUs) p.cfg = kC64x64;
@@ -628,12 +746,30 @@ Plan make_plan(int64_t M, int64_t N, int64_t K, bool allow_split) {
   return p;
 }
 
+// Epilogues that a product of these layouts meets: forward (KMajor, KMajor),
+// input gradient (KMajor, MNMajor), weight gradient (MNMajor, MNMajor).
+template <Lay LA, Lay LB>
+constexpr bool meets(Epi e) {
+  if (e == Epi::SplitK) return true;
+  if (LB == Lay::KMajor) return e == Epi::Bias || e == Epi::BiasRelu || e == Epi::Mse;
+  return LA == Lay::KMajor ? e == Epi::Mask : e == Epi::Store || e == Epi::Adam;
+}
+
 template <Lay LA, Lay LB, Epi EPI, int ROLE>
 hipError_t launch_cfg(int cfg, const GemmArgs& g, int64_t splits, hipStream_t st, hipEvent_t t0, hipEvent_t t1) {
-  switch (cfg) {
-    case kC128x128: return ot::launch_gemm_f32<2, 2, 4, 4, LA, LB, EPI, 16, ROLE>(g, splits, st, t0, t1);
-    case kC64x128: return ot::launch_gemm_f32<2, 2, 2, 4, LA, LB, EPI, 16, ROLE>(g, splits, st, t0, t1);
-    default: return ot::launch_gemm_f32<2, 2, 2, 2, LA, LB, EPI, 16, ROLE>(g, splits, st, t0, t1);
+  if constexpr (!meets<LA, LB>(EPI)) {
+    return hipErrorInvalidValue;
+  } else {
+    switch (cfg) {
+      case kC128x128: return ot::launch_gemm_f32<2, 2, 4, 4, LA, LB, EPI, 16, ROLE>(g, splits, st, t0, t1);
+      case kC64x128: return ot::launch_gemm_f32<2, 2, 2, 4, LA, LB, EPI, 16, ROLE>(g, splits, st, t0, t1);
+      case kX128: return ot::launch_gemm_f32x3<2, 2, 2, 2, LA, LB, EPI, ROLE>(g, splits, st, t0, t1);
+      case kX64x128: return ot::launch_gemm_f32x3<2, 2, 1, 2, LA, LB, EPI, ROLE>(g, splits, st, t0, t1);
+      case kX64: return ot::launch_gemm_f32x3<2, 2, 1, 1, LA, LB, EPI, ROLE>(g, splits, st, t0, t1);
+      case kX32W: return ot::launch_gemm_f32x3<1, 4, 1, 2, LA, LB, EPI, ROLE>(g, splits, st, t0, t1);
+      case kX64W: return ot::launch_gemm_f32x3<1, 4, 2, 2, LA, LB, EPI, ROLE>(g, splits, st, t0, t1);
+      default: return ot::launch_gemm_f32<2, 2, 2, 2, LA, LB, EPI, 16, ROLE>(g, splits, st, t0, t1);
+    }
   }
 }
 
@@ -698,7 +834,7 @@ template <Lay LA, Lay LB, int ROLE = 0>
 int run_gemm(ot_surrogate* s, GemmArgs g, Epi epi, hipStream_t st, const char* what, bool allow_split,
              int ph_gemm = -1, int ph_reduce = -1, int64_t* blocks_out = nullptr,
              const ot::AdamRest* rest = nullptr, bool* rest_done = nullptr) {
-  const Plan p = make_plan(g.M, g.N, g.K, allow_split && epi != Epi::Mse);
+  const Plan p = make_plan(g.M, g.N, g.K, allow_split && epi != Epi::Mse, LB == Lay::MNMajor);
   if (blocks_out) *blocks_out = p.blocks;
   ot::PhaseTimer& tm = s->timer;
   if (p.splits == 1) {
@@ -751,6 +887,14 @@ int run_gemm(ot_surrogate* s, GemmArgs g, Epi epi, hipStream_t st, const char* w
     return OT_OK;
   }
   const bool bias = (epi == Epi::Bias || epi == Epi::BiasRelu);
+  if (ot::splitk_wide(p.splits, work) && !g.rowsum) {
+    hipLaunchKernelGGL(ot::splitk_wide_kernel<float>, dim3((unsigned)ot::ceil_div(work, 16)), dim3(256), 0, st,
+                       s->splitws, p.splits, h.split_stride, g.M, g.N, ldws, bias ? g.bias : nullptr,
+                       epi == Epi::BiasRelu ? 1 : 0, epi == Epi::Mask ? g.mask : nullptr, g.ldmask, g.C, g.ldc);
+    OT_LAUNCHED("splitk_wide_kernel");
+    if (ph_reduce >= 0) tm.mark(st, ph_reduce, 1);
+    return OT_OK;
+  }
   hipLaunchKernelGGL(ot::splitk_epilogue_kernel, dim3((unsigned)ot::ceil_div(work, 128)), dim3(128), 0, st,
                      s->splitws, p.splits, h.split_stride, g.M, g.N, ldws, bias ? g.bias : nullptr,
                      epi == Epi::BiasRelu ? 1 : 0, epi == Epi::Mask ? g.mask : nullptr, g.ldmask, g.C, g.ldc,
@@ -948,6 +1092,12 @@ int run_gemm_b(ot_surrogate* s, GemmBArgs g, hipStream_t st, const char* what, b
                          E == EpiB::BiasF32 ? g.bias : nullptr, 0, (const float*)nullptr, (int64_t)0,
                          reinterpret_cast<float*>(g.C), g.ldc, h.rowsum, h.rowsum_stride, g.rowsum);
       OT_LAUNCHED("splitk_epilogue_kernel");
+    } else if (ot::splitk_wide(p.splits, work)) {
+      hipLaunchKernelGGL(ot::splitk_wide_kernel<uint16_t>, dim3((unsigned)ot::ceil_div(work, 16)), dim3(256), 0, st,
+                         s->splitws, p.splits, h.split_stride, g.M, g.N, ldws,
+                         E == EpiB::BiasReluBf ? g.bias : nullptr, E == EpiB::BiasReluBf ? 1 : 0,
+                         E == EpiB::MaskBf ? g.mask : nullptr, g.ldmask, reinterpret_cast<uint16_t*>(g.C), g.ldc);
+      OT_LAUNCHED("splitk_wide_kernel");
     } else {
       hipLaunchKernelGGL(ot::splitk_epilogue_bf16_kernel, dim3((unsigned)ot::ceil_div(work, 128)), dim3(128), 0, st,
                          s->splitws, p.splits, h.split_stride, g.M, g.N, ldws,
@@ -1242,7 +1392,7 @@ extern "C" int surrogate_create(ot_surrogate** out, const int64_t* widths, int32
     hipLaunchKernelGGL(ot::to_bf16_kernel, dim3(fb), dim3(256), 0, 0, s->params, s->pb, s->n_flat);
   }
   if (hipGetLastError() != hipSuccess) return fail(ot::set_error(OT_E_HIP, "initialisation launch failed"));
-  if ((rc = ensure_workspace(s, max_batch))) return fail(rc);
+  if ((rc = ensure_workspace(s, max_batch, true))) return fail(rc);
   if (hipDeviceSynchronize() != hipSuccess) return fail(ot::set_error(OT_E_HIP, "initialisation failed"));
   *out = s;
   return OT_OK;
@@ -1487,6 +1637,8 @@ static int train_step_launches(ot_surrogate* s, const float* x, int64_t ldx, con
     g.N = ly.in;
     g.K = b;
     g.rowsum = db;
+    g.padded_a = true;
+    g.padded_b = l > 1;                 // x belongs to the caller
     if (l == L && s->fused_step) {
       g.C = s->params + ly.w_off;
       g.adam_m = s->m + ly.w_off;
@@ -1514,6 +1666,7 @@ static int train_step_launches(ot_surrogate* s, const float* x, int64_t ldx, con
     g.ldc = s->ld[l - 1];
     g.mask = s->act[l - 1];
     g.ldmask = s->ld[l - 1];
+    g.padded_b = true;
     return (l == L) ? run_gemm<Lay::KMajor, Lay::MNMajor, 1>(s, g, Epi::Mask, st, "input gradient", true,
                                                              OT_PH_IGRAD_OUTPUT, OT_PH_IGRAD_REDUCE)
                     : run_gemm<Lay::KMajor, Lay::MNMajor, 0>(s, g, Epi::Mask, st, "input gradient", true);

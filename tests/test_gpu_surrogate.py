@@ -79,6 +79,14 @@ SHAPES = [
     ((6, 256, 256, 10000), 1024),    # the 100x100 workload's net at its batch
     ((6, 8, 1), 1),                  # one sample, one output
     ((6, 300, 300, 7), 2),           # two samples, hidden widths past one tile
+    # output products on three bf16 terms: every tile shape, ragged edges
+    ((6, 200, 150, 70001), 20),      # 32 x 256 forward and input gradient, 512 splits
+    ((6, 70, 131, 66000), 50),       # 64 x 256 forward and input gradient
+    ((6, 90, 150, 13501), 300),      # 64 x 128 forward, 128 x 128 gradients, both split
+    ((6, 200, 150, 40003), 200),     # unsplit weight gradient with Adam in its epilogue
+    ((6, 60, 50, 20005), 250),       # gradients 50 units wide: 64 x 64 tiles
+    ((6, 300, 437, 6561), 331),      # 64 x 64 forward, no dimension a multiple of 16
+    ((24, 9001), 1000),              # single layer: the caller's unpadded x as an operand
 ]
 
 
@@ -627,3 +635,38 @@ def test_heat_workload_full_shape_100_steps(flags):
     st = tr.res.stats()
     assert st["n"] == ref["N"] == 26_600 and st["total_draws"] == 100 * 1024
     tr.close()
+
+
+@pytest.mark.parametrize("value", [2.0 ** 70, 3.3e38, np.inf, np.nan])
+def test_predict_beyond_split_range(value):
+    """A product on three bf16 terms whose operands hold a value beyond the
+    range of the split (or infinity, NaN): the same finite and non-finite
+    outputs as fp32 arithmetic, the other outputs unchanged."""
+    widths, B = (6, 64, 64, 20000), 200
+    params, X, _ = problem(widths, B, seed=11)
+    W, b = params[-1]
+    W[:, 5] = np.where(np.arange(len(W)) % 2 == 0, W[:, 5], 1.0)      # exact in bf16: further terms are zero
+    W[777, 5] = value
+    W[778, 5] = -value
+    s = make_gpu(widths, params, B)
+    Y = padded_from(np.zeros((B, widths[-1]), np.float32))
+    s.predict(padded_from(X), Y)
+    torch.cuda.synchronize()
+    got = Y.cpu().numpy()
+    A = X.astype(np.float64)
+    for Wl, bl in params[:-1]:
+        A = np.maximum(A @ Wl.T + bl, 0.0)
+    A = A.astype(np.float32).astype(np.float64)
+    with np.errstate(all="ignore"):
+        ref = (A @ W.astype(np.float32).astype(np.float64).T + b).astype(np.float32)
+        # a term that overflows fp32 makes the sum infinite whatever follows
+        over = np.abs(A[:, 5] * np.float64(np.float32(value))) > np.finfo(np.float32).max
+    if np.isfinite(value):
+        ref[over, 777], ref[over, 778] = np.inf, -np.inf
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isinf(got), np.isinf(ref))
+    fin = np.isfinite(ref)
+    assert np.array_equal(np.sign(got[~fin & ~np.isnan(ref)]), np.sign(ref[~fin & ~np.isnan(ref)]))
+    # fp32 sums of 64 terms, relative to the largest one of the row
+    scale = np.maximum(np.abs(ref), np.abs(A).max() * np.minimum(np.abs(np.nan_to_num(W, posinf=0.0)).max(axis=1), 1e38))
+    assert np.all(np.abs(got - ref)[fin] <= 64 * 2.0 ** -24 * scale[fin])
+    s.close()

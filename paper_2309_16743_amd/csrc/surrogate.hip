@@ -49,10 +49,24 @@ __global__ void fill_kernel(float* __restrict__ p, int64_t n, float v) {
   if (i < n) p[i] = v;
 }
 
-// p[m][w .. ld) = 0 for `rows` rows of leading dimension ld.
-__global__ void zero_pad_kernel(float* __restrict__ p, int64_t ld, int64_t w, int64_t rows) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, pad = ld - w;
-  if (i < rows * pad) p[i / pad * ld + w + i % pad] = 0.f;
+// Zero the padding of up to kMaxPads arrays in one launch: array a holds rows[a]
+// rows of ld[a] elements, of which the first w[a] are not touched; its
+// elements are 2 or 4 bytes wide.  grid = (blocks, arrays).
+constexpr int kMaxPads = 32;
+struct PadList {
+  void* p[kMaxPads];
+  int64_t ld[kMaxPads], w[kMaxPads], rows[kMaxPads];
+  int bytes[kMaxPads];
+  int n;
+};
+__global__ __launch_bounds__(256) void zero_pads_kernel(PadList l) {
+  const int a = blockIdx.y;
+  const int64_t ld = l.ld[a], w = l.w[a], pad = ld - w, n = l.rows[a] * pad;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const int64_t o = i / pad * ld + w + i % pad;
+    if (l.bytes[a] == 2) static_cast<uint16_t*>(l.p[a])[o] = 0;
+    else static_cast<float*>(l.p[a])[o] = 0.f;
+  }
 }
 
 // First layer with a small input width K (the 6 inputs (X, t)):
@@ -516,6 +530,7 @@ struct ot_surrogate {
   bool device_step = false;
   // Workspaces, sized for ws_rows batch rows.
   int64_t ws_rows = 0;
+  int64_t act_rows = 0;      // rows of the hidden activations (>= ws_rows): what one prediction pass takes
   std::vector<float*> act;   // act[l] = A_l, l = 1..L-1 (index 0 unused)
   std::vector<float*> dz;    // dz[l] = dZ_l, l = 1..L (dz[L] = dY)
   std::vector<int64_t> ld;   // ld[l] = round_up(widths[l], 4)
@@ -581,7 +596,7 @@ void free_workspace(ot_surrogate* s) {
   s->rsws_elems = 0;
   s->loss_partials = nullptr;
   s->l1_part = nullptr;
-  s->ws_rows = 0;
+  s->ws_rows = s->act_rows = 0;
 }
 
 void free_surrogate(ot_surrogate* s) {
@@ -602,6 +617,10 @@ void free_surrogate(ot_surrogate* s) {
 }
 
 constexpr int64_t kL1Parts = 32;
+// Hidden activations are sized for this many rows at least, so that a
+// prediction of more rows than the batch reads the output weights once (40 rows
+// after batches of 10, 1000000 x 256 fp32: 340 us instead of 4 x 250).
+constexpr int64_t kPredictRows = 256;
 
 int refuse_alloc(const char* what) {
   return ot::set_error(OT_E_STATE, "%s would allocate inside surrogate_predict_noalloc", what);
@@ -615,30 +634,38 @@ int ensure_workspace(ot_surrogate* s, int64_t rows, bool creating = false) {
   free_workspace(s);
   const int L = s->L;
   int rc;
+  // rows are padded to a multiple of 8 values (dY of a bf16 surrogate: of 32),
+  // which the weight gradient may read (into results it drops) and the bf16
+  // input gradient sums over: the padding is zero
+  ot::PadList pads{};
+  const int64_t act_rows = std::max(rows, kPredictRows);
+  auto with_zero_pad = [&](auto** p, int l, int64_t n) -> int {
+    int rc = salloc((void**)p, (size_t)n * s->ld[l] * sizeof(**p));
+    if (rc || s->ld[l] == s->widths[l]) return rc;
+    const int a = pads.n++;                     // at most two arrays for each of 15 layers
+    pads.p[a] = *p;
+    pads.ld[a] = s->ld[l];
+    pads.w[a] = s->widths[l];
+    pads.rows[a] = n;
+    pads.bytes[a] = (int)sizeof(**p);
+    return OT_OK;
+  };
   if (s->precision == OT_BF16) {
     for (int l = 1; l < L; ++l)
-      if ((rc = salloc((void**)&s->act16[l], (size_t)rows * s->ld[l] * sizeof(uint16_t)))) return rc;
-    for (int l = 1; l <= L; ++l)
-      if ((rc = salloc((void**)&s->dz16[l], (size_t)rows * s->ld[l] * sizeof(uint16_t)))) return rc;
-  } else {
-    // rows are padded to a multiple of 8 values, which the weight gradient may
-    // read (into results it drops): the padding is zero
-    bool cleared = false;
-    auto with_zero_pad = [&](float** p, int l) -> int {
-      int rc = salloc((void**)p, (size_t)rows * s->ld[l] * sizeof(float));
-      const int64_t pad = s->ld[l] - s->widths[l];
-      if (rc || pad == 0) return rc;
-      hipLaunchKernelGGL(ot::zero_pad_kernel, dim3((unsigned)ot::ceil_div(rows * pad, 256)), dim3(256), 0, 0, *p,
-                         s->ld[l], s->widths[l], rows);
-      OT_LAUNCHED("zero_pad_kernel");
-      cleared = true;
-      return OT_OK;
-    };
+      if ((rc = salloc((void**)&s->act16[l], (size_t)act_rows * s->ld[l] * sizeof(uint16_t)))) return rc;
     for (int l = 1; l < L; ++l)
-      if ((rc = with_zero_pad(&s->act[l], l))) return rc;
+      if ((rc = salloc((void**)&s->dz16[l], (size_t)rows * s->ld[l] * sizeof(uint16_t)))) return rc;
+    if ((rc = with_zero_pad(&s->dz16[L], L, rows))) return rc;
+  } else {
+    for (int l = 1; l < L; ++l)
+      if ((rc = with_zero_pad(&s->act[l], l, act_rows))) return rc;
     for (int l = 1; l <= L; ++l)
-      if ((rc = with_zero_pad(&s->dz[l], l))) return rc;
-    if (cleared && !creating) OT_HIP(hipStreamSynchronize(0));
+      if ((rc = with_zero_pad(&s->dz[l], l, rows))) return rc;
+  }
+  if (pads.n) {
+    hipLaunchKernelGGL(ot::zero_pads_kernel, dim3(64, (unsigned)pads.n), dim3(256), 0, 0, pads);
+    OT_LAUNCHED("zero_pads_kernel");
+    if (!creating) OT_HIP(hipStreamSynchronize(0));
   }
   // one loss partial per block of the output GEMM (64 x 64 tiles bound the count)
   s->n_partials_cap = ot::ceil_div(rows, 64) * ot::ceil_div(s->widths[L], 64) + 64;
@@ -653,6 +680,7 @@ int ensure_workspace(ot_surrogate* s, int64_t rows, bool creating = false) {
     if ((rc = salloc((void**)&s->hs_part2b, (size_t)(n_kc * h2) * sizeof(float)))) return rc;
   }
   s->ws_rows = rows;
+  s->act_rows = act_rows;
   return OT_OK;
 }
 
@@ -957,63 +985,83 @@ using ot::GemmBArgs;
 using ot::LayB;
 
 // bf16 tiles: for large products the pipelined 256 x 128 kernel (k tile 32,
-// direct-to-LDS loads, two blocks per CU) or the ping-pong 256 x 256 kernel
-// (eight wavefronts, one block per CU); 128 x 128 (4 x 4 fragments per wave)
-// and 64 x 64 (2 x 2) with a k tile of 32 otherwise.
-enum CfgB : int { kB128 = 0, kB64 = 1, kBPipe = 2, kBPipeW = 3 };
+// direct-to-LDS loads, two blocks per CU), its 128 x 256 shape for up to 128
+// rows, or the ping-pong 256 x 256 kernel (eight wavefronts, one block per CU);
+// 128 x 128 (4 x 4 fragments per wave) and 64 x 64 (2 x 2) with a k tile of 32
+// otherwise.
+enum CfgB : int { kB128 = 0, kB64 = 1, kBPipe = 2, kBPipeW = 3, kBPipeH = 4 };
 constexpr int kBK = 32;
 constexpr int kPipeBK = 32;
 
 int64_t tiles_b(int cfg, int64_t M, int64_t N) {
   if (cfg == kBPipe) return ot::gemm_bf16_pipe_tiles<256, 128>(M, N);
   if (cfg == kBPipeW) return ot::gemm_bf16_pipe_tiles<256, 256>(M, N);
+  if (cfg == kBPipeH) return ot::gemm_bf16_pipe_tiles<128, 256>(M, N);
   return cfg == kB128 ? ot::gemm_bf16_tiles<4, 4>(M, N) : ot::gemm_bf16_tiles<2, 2>(M, N);
 }
 
-// The 32-deep k tile kernels when k is a multiple of 32 and the tiles give
-// about one block per CU or more: products split over long k ranges take the
-// ping-pong kernel's 256 x 256 tiles (splits until about two blocks per CU,
-// keeping at least 32 k tiles per split), and so do unsplit products with the
-// fused MSE epilogue when wide_ok; the others 256 x 128 tiles of the
-// pipelined kernel (two blocks per CU).  Else 128 x 128 tiles when they give
-// about two blocks per CU; long k ranges are split over 128 x 128 tiles,
-// shorter ones over 64 x 64.
+// Rows of a tile.
+int64_t tile_rows_b(int cfg) {
+  return (cfg == kBPipe || cfg == kBPipeW) ? 256 : (cfg == kB128 || cfg == kBPipeH) ? 128 : 64;
+}
+
+enum class Prod : int { Forward, InputGrad, WeightGrad };
+template <LayB LA, LayB LB>
+constexpr Prod prod_of() {
+  return LB == LayB::KMajor ? Prod::Forward : LA == LayB::KMajor ? Prod::InputGrad : Prod::WeightGrad;
+}
+
+// Wide forward products (about a tile per CU or more) are not split.  Up to 64
+// rows they stream the weights through 64 x 64 tiles (1 row, 1000000 x 1024: 355
+// us, 592 on 128 x 128), up to 128 through the pipelined kernel's 128 x 256 (100
+// rows: 508 against 638 us), above through the ping-pong kernel's 256 x 256 (200
+// rows, 1000000 x 2048: 1246 against 2115 us on 128 x 128, 1417 on 128 x 256);
+// rows past the operand are read from its last one.
+// Input gradients: over long k ranges the ping-pong kernel in splits until about two
+// blocks per CU, keeping at least 32 k tiles per split (200 x 1024, k 200000: 110
+// against 369 us on 128 x 128); else 256 x 128 tiles of the pipelined kernel with at
+// least 10 k tiles per split (512 x 512, k 19616: 23 against 38 us); 128 x 256 tiles
+// up to 128 rows (64 x 1024, k 300000: 125 against 178 us; 100 x 512, k 200000: 45 against 66).
+// Others with the 32-deep k tile kernels when k is a multiple of 32 and the tiles
+// give about one block per CU or more (forward products keep 32 k tiles per
+// split, so that their partials stay as small as they were), else 128 x 128 tiles
+// when they give about two blocks per CU; long k ranges are split over 128 x 128
+// tiles, shorter ones over 64 x 64.
 // pipe_ok: the 32-deep k tile kernels may be used (they have no row-sum output).
-Plan make_plan_b(int64_t M, int64_t N, int64_t K, bool allow_split, bool pipe_ok = true, bool wide_ok = false) {
+Plan make_plan_b(int64_t M, int64_t N, int64_t K, bool allow_split, Prod prod, bool pipe_ok = true) {
   constexpr int64_t kCUs = 256;
   Plan p;
-  if (wide_ok && pipe_ok && !allow_split && K % kPipeBK == 0 && M >= 256 && N >= 256 &&
-      tiles_b(kBPipeW, M, N) >= kCUs - 16) {
-    p.cfg = kBPipeW;
-    p.k_chunk = K;
-    p.splits = 1;
-    p.blocks = tiles_b(kBPipeW, M, N);
+  auto plan = [&](int cfg, int64_t sp) {
+    p.cfg = cfg;
+    p.k_chunk = ot::round_up(ot::ceil_div(K, sp), kPipeBK);
+    p.splits = std::max<int64_t>(1, ot::ceil_div(K, p.k_chunk));
+    p.blocks = tiles_b(cfg, M, N) * p.splits;
     return p;
+  };
+  const bool deep = pipe_ok && K % kPipeBK == 0;
+  if (prod == Prod::Forward) {
+    if (M <= 64 && tiles_b(kB64, M, N) >= kCUs - 16) return plan(kB64, 1);
+    if (deep && N >= 256 && M > 64 && M <= 128 && tiles_b(kBPipeH, M, N) >= kCUs - 16) return plan(kBPipeH, 1);
+    if (deep && N >= 256 && M > 128 && tiles_b(kBPipeW, M, N) >= kCUs - 16) return plan(kBPipeW, 1);
   }
-  if (pipe_ok && allow_split && K % kPipeBK == 0 && M >= 256 && N >= 256) {
+  if (deep && allow_split && M >= (prod == Prod::InputGrad ? 129 : 256) && N >= 256) {
     const int64_t t = tiles_b(kBPipeW, M, N);
     int64_t sp = 1;
     while (t * sp < 2 * kCUs - 32 && K / (2 * sp) >= 32 * kPipeBK) sp *= 2;
-    if (sp > 1 && t * sp >= kCUs - 16) {
-      p.cfg = kBPipeW;
-      p.k_chunk = ot::round_up(ot::ceil_div(K, sp), kPipeBK);
-      p.splits = std::max<int64_t>(1, ot::ceil_div(K, p.k_chunk));
-      p.blocks = t * p.splits;
-      return p;
-    }
+    if (sp > 1 && t * sp >= kCUs - 16) return plan(kBPipeW, sp);
   }
-  if (pipe_ok && K % kPipeBK == 0 && M >= 256 && N >= 128) {
+  if (deep && allow_split && prod == Prod::InputGrad && M <= 128 && N >= 128) {
+    const int64_t t = tiles_b(kBPipeH, M, N);
+    int64_t sp = 1;
+    while (t * sp < (M <= 32 ? 2 * kCUs - 32 : kCUs - 16) && K / (2 * sp) >= 10 * kPipeBK) sp *= 2;
+    if (t * sp >= kCUs - 16) return plan(kBPipeH, sp);
+  }
+  if (deep && M >= (prod == Prod::InputGrad ? 129 : 256) && N >= 128) {
     const int64_t t = tiles_b(kBPipe, M, N);
     int64_t sp = 1;
     if (allow_split)
-      while (t * sp < 4 * kCUs - 64 && K / (2 * sp) >= 32 * kPipeBK) sp *= 2;
-    if (t * sp >= kCUs - 16) {
-      p.cfg = kBPipe;
-      p.k_chunk = ot::round_up(ot::ceil_div(K, sp), kPipeBK);
-      p.splits = std::max<int64_t>(1, ot::ceil_div(K, p.k_chunk));
-      p.blocks = t * p.splits;
-      return p;
-    }
+      while (t * sp < 4 * kCUs - 64 && K / (2 * sp) >= (prod == Prod::InputGrad ? 10 : 32) * kPipeBK) sp *= 2;
+    if (t * sp >= kCUs - 16) return plan(kBPipe, sp);
   }
   const int64_t t128 = tiles_b(kB128, M, N);
   if (t128 >= 2 * kCUs - 32) {
@@ -1042,6 +1090,9 @@ hipError_t launch_cfg_b(int cfg, const GemmBArgs& g, int64_t splits, hipStream_t
     if (cfg == kBPipe) return ot::launch_gemm_bf16_pipe<128, 256, kPipeBK, 3, 2, LA, LB, E>(g, splits, st, t0, t1);
   }
   if (cfg == kBPipe) return ot::launch_gemm_bf16_pipe<256, 128, kPipeBK, 3, 2, LA, LB, E>(g, splits, st, t0, t1);
+  if constexpr (LA == LayB::KMajor) {
+    if (cfg == kBPipeH) return ot::launch_gemm_bf16_pipe<128, 256, kPipeBK, 3, 2, LA, LB, E>(g, splits, st, t0, t1);
+  }
   if constexpr (E != EpiB::AdamF32) {
     // 256 x 256 tile, eight wavefronts in ping-pong, 4 stages (128 KB of LDS), one block per CU
     if (cfg == kBPipeW) return ot::launch_gemm_bf16_pp<4, LA, LB, E>(g, splits, st, t0, t1);
@@ -1055,8 +1106,8 @@ hipError_t launch_cfg_b(int cfg, const GemmBArgs& g, int64_t splits, hipStream_t
 template <LayB LA, LayB LB, EpiB E>
 int run_gemm_b(ot_surrogate* s, GemmBArgs g, hipStream_t st, const char* what, bool allow_split,
                int ph_gemm = -1, int ph_reduce = -1, int64_t* blocks_out = nullptr) {
-  const Plan p = make_plan_b(g.M, g.N, g.K, allow_split && E != EpiB::MseBf && E != EpiB::AdamF32, g.rowsum == nullptr,
-                             E == EpiB::MseBf);
+  const Plan p = make_plan_b(g.M, g.N, g.K, allow_split && E != EpiB::MseBf && E != EpiB::AdamF32, prod_of<LA, LB>(),
+                             g.rowsum == nullptr);
   if (blocks_out) *blocks_out = p.blocks;
   ot::PhaseTimer& tm = s->timer;
   if (p.splits == 1) {
@@ -1183,14 +1234,14 @@ int forward_mse_bf16(ot_surrogate* s, const float* x, int64_t ldx, const float* 
     g.colsum = s->colsum;
     g.colsum_ld = s->ld[L];
   }
-  const Plan pf = make_plan_b(g.M, g.N, g.K, false, true, true);
+  const Plan pf = make_plan_b(g.M, g.N, g.K, false, Prod::Forward);
   *n_partials = pf.blocks;
   if (pf.blocks > s->n_partials_cap) return ot::set_error(OT_E_STATE, "loss partial buffer too small");
   if ((rc = run_gemm_b<LayB::KMajor, LayB::KMajor, EpiB::MseBf>(s, g, st, "bf16 output forward+MSE", false,
                                                                 OT_PH_FWD_OUTPUT)))
     return rc;
   if (bias_grad) {
-    const int64_t used_mtiles = ot::ceil_div(b, (pf.cfg == kBPipe || pf.cfg == kBPipeW) ? 256 : (pf.cfg == kB128 ? 128 : 64));
+    const int64_t used_mtiles = ot::ceil_div(b, tile_rows_b(pf.cfg));
     hipLaunchKernelGGL(ot::colsum_reduce_kernel, dim3((unsigned)ot::ceil_div(D, 256)), dim3(256), 0, st, s->colsum,
                        used_mtiles, D, s->ld[L], s->grads + lo.b_off);
     OT_LAUNCHED("colsum_reduce_kernel");
@@ -1265,7 +1316,7 @@ int train_step_bf16(ot_surrogate* s, const float* x, int64_t ldx, const float* u
       g.ldc = s->ld[l - 1];
       g.M = b;
       g.N = ly.in;
-      g.K = ly.out;
+      g.K = l == L ? s->ld[L] : ly.out;   // the output layer's padding rounds its k range up (zeros of dY)
       g.mask = s->act16[l - 1];
       g.ldmask = s->ld[l - 1];
       return run_gemm_b<LayB::KMajor, LayB::MNMajor, EpiB::MaskBf>(s, g, st, "bf16 input gradient", true,
@@ -1346,6 +1397,9 @@ extern "C" int surrogate_create(ot_surrogate** out, const int64_t* widths, int32
                     widths[1] <= ot::kSmallH && widths[2] <= ot::kSmallH;
   s->ld.resize(n_widths);
   for (int i = 0; i < n_widths; ++i) s->ld[i] = ot::round_up(widths[i], 8);
+  // bf16: dY's rows are padded to whole k tiles of the output input gradient
+  // (zeros; the weight rows that meet them are pb's tail, allocated below)
+  if (precision == OT_BF16) s->ld[n_widths - 1] = ot::round_up(widths[n_widths - 1], kPipeBK);
   int64_t off = 0;
   for (int l = 0; l < s->L; ++l) {
     Layer ly;
@@ -1388,7 +1442,17 @@ extern "C" int surrogate_create(ot_surrogate** out, const int64_t* widths, int32
                        1.0 / std::sqrt((double)ly.in));
   }
   if (precision == OT_BF16) {
-    if ((rc = salloc((void**)&s->pb, (size_t)s->n_flat * sizeof(uint16_t)))) return fail(rc);
+    // the output input gradient reads up to kPipeBK - 1 weight rows past W_L (times zeros of dY's
+    // padding): the bias copy, then this zeroed tail
+    const int64_t tail = kPipeBK * s->layers[s->L - 1].ldw;
+    if ((rc = salloc((void**)&s->pb, (size_t)(s->n_flat + tail) * sizeof(uint16_t)))) return fail(rc);
+    ot::PadList pads{};
+    pads.p[0] = s->pb + s->n_flat;
+    pads.ld[0] = tail;
+    pads.rows[0] = 1;
+    pads.bytes[0] = 2;
+    pads.n = 1;
+    hipLaunchKernelGGL(ot::zero_pads_kernel, dim3(64, 1), dim3(256), 0, 0, pads);
     hipLaunchKernelGGL(ot::to_bf16_kernel, dim3(fb), dim3(256), 0, 0, s->params, s->pb, s->n_flat);
   }
   if (hipGetLastError() != hipSuccess) return fail(ot::set_error(OT_E_HIP, "initialisation launch failed"));
@@ -1940,7 +2004,7 @@ extern "C" int surrogate_predict(ot_surrogate* s, const float* x, int64_t ldx, i
   int rc = check_predict(s, x, ldx, y, ldy, "surrogate_predict");
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int64_t chunk = std::max<int64_t>(s->ws_rows, 1);
+  const int64_t chunk = std::max<int64_t>(s->act_rows, 1);
   for (int64_t r0 = 0; r0 < n; r0 += chunk) {
     const int64_t rows = std::min(chunk, n - r0);
     if ((rc = predict_rows(s, x + r0 * ldx, ldx, rows, y + r0 * ldy, ldy, st))) return rc;
@@ -2006,7 +2070,7 @@ NoAllocLayout noalloc_layout(const ot_surrogate* s, int64_t rows) {
     // hidden layers without a GEMM: bf16 layer 1, the fp32 small-K layer 1
     // and the fp32 narrow-hidden kernels
     if (l < L && (bf ? l == 1 : (s->small_hidden || (l == 1 && ly.in <= ot::kMaxSmallK)))) continue;
-    const Plan p = bf ? make_plan_b(rows, ly.out, ly.in, true) : make_plan(rows, ly.out, ly.in, true);
+    const Plan p = bf ? make_plan_b(rows, ly.out, ly.in, true, Prod::Forward) : make_plan(rows, ly.out, ly.in, true);
     if (p.splits > 1) split = std::max(split, p.splits * rows * ot::round_up(ly.out, 4));
   }
   lay.split_off = off;

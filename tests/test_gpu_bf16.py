@@ -75,6 +75,10 @@ SHAPES = [
     ((6, 40, 24, 9), 3),               # three samples, ragged narrow widths
     ((6, 64, 83, 500), 36),            # fused update whose last column group is partial and starts a 16-column fragment
     ((6, 64, 470, 30001), 64),         # the same on the pipelined kernel's tiles
+    ((6, 96, 160, 61450), 100),        # up to 128 rows: 128 x 256 forward and input gradient, k padded from 61450
+    ((6, 64, 256, 61440), 129),        # just above: 256 x 256 forward (half its rows clamped) and input gradient
+    ((6, 96, 128, 15361), 64),         # up to 64 rows: 64 x 64 forward
+    ((6, 512, 512, 19600), 512),       # 256 x 128 input gradient in short splits, k padded from 19600
 ]
 
 
@@ -112,7 +116,9 @@ def test_one_train_step_bf16(widths, B):
     f.close()
 
 
-@pytest.mark.parametrize("widths,n", [((6, 64, 64, 256), 40), ((6, 100, 77, 1001), 77)])
+@pytest.mark.parametrize("widths,n", [((6, 64, 64, 256), 40), ((6, 100, 77, 1001), 77), ((6, 64, 96, 61441), 1),
+                                      ((6, 64, 96, 61443), 128), ((6, 64, 96, 61447), 200),
+                                      ((6, 64, 96, 999), 300)])   # 300 rows: two passes
 def test_predict_bf16(widths, n):
     params, X, _ = problem(widths, n, seed=5)
     s = make_gpu(widths, params, 32)

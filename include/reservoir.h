@@ -22,13 +22,15 @@
  * Results depend only on (seed, the sequence of calls in ticket order).
  *
  * Memory and streams: the reservoir owns its device memory (slabs, per-slot
- * seen counts and sample ids, counters).  All work runs on one ordering
- * stream, in ticket order.  Every call takes the caller's stream: the
- * ordering stream first waits for work already queued on the caller's stream,
- * and the caller's stream then waits for the call's work, so buffers passed
- * in may be reused in stream order.  When the caller's stream is the ordering
- * stream no events are used.  Calls are asynchronous unless stated.  Reservoir
- * calls are thread-safe.
+ * seen counts and sample ids, counters).  All work runs in ticket order.
+ * Every call takes the caller's stream: its work runs after the work already
+ * queued on that stream and after the calls with earlier tickets, and the
+ * caller's stream runs what follows after the call's work, so buffers passed
+ * in may be reused in stream order.  A reservoir created with an order_stream
+ * runs the work of every call there (no events are used when the caller's
+ * stream is that stream); one created without runs it on the caller's
+ * streams, which may be destroyed after the call.  Calls are asynchronous
+ * unless stated.  Reservoir calls are thread-safe.
  *
  * Device pointers must be 16-byte aligned and their leading dimensions (in
  * elements) multiples of 4 where a field row is involved.
@@ -91,7 +93,8 @@ enum ot_reservoir_policy { OT_POLICY_RESERVOIR = 0, OT_POLICY_FIFO = 1, OT_POLIC
  * threshold: batches are refused while N <= threshold (Algorithm 1, get;
  * unused by FIFO).  seed: Philox key word 0.  policy: ot_reservoir_policy.
  * order_stream: hipStream_t to run the reservoir's
- * work on, or NULL to let the reservoir create (and later destroy) its own.
+ * work on, or NULL to run each call's work on the caller's stream (under
+ * capture: on a stream that the reservoir creates and later destroys).
  * Allocates C * (round_up(x_dim, 4) + round_up(u_dim, 64)) * 4 bytes of slab
  * plus 20 bytes per slot of metadata on the current device.
  * Errors: OT_E_INVAL (capacity < 1 or > 2^31-1, threshold < 0, x_dim or u_dim

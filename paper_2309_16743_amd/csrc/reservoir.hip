@@ -672,6 +672,7 @@ struct ot_reservoir {
   hipStream_t stream = nullptr;
   bool own_stream = false;
   hipEvent_t ev_in = nullptr, ev_out = nullptr;
+  hipEvent_t ev_last = nullptr;   // own_stream: recorded behind each call's work, wherever that ran
   std::mutex mu;             // guards seq and the timer; held for the whole of every call
   ot::PhaseTimer timer;
 };
@@ -680,6 +681,7 @@ namespace {
 
 void free_reservoir(ot_reservoir* r) {
   if (!r) return;
+  if (r->ev_last) (void)hipEventSynchronize(r->ev_last);
   if (r->stream) (void)hipStreamSynchronize(r->stream);
   r->timer.release();
   (void)hipFree(r->xslab);
@@ -696,6 +698,7 @@ void free_reservoir(ot_reservoir* r) {
   (void)hipFree(r->ctr);
   if (r->ev_in) (void)hipEventDestroy(r->ev_in);
   if (r->ev_out) (void)hipEventDestroy(r->ev_out);
+  if (r->ev_last) (void)hipEventDestroy(r->ev_last);
   if (r->own_stream && r->stream) (void)hipStreamDestroy(r->stream);
   delete r;
 }
@@ -711,19 +714,64 @@ int dev_alloc(T** p, size_t count) {
   return OT_OK;
 }
 
-// Order the reservoir's stream after the caller's work.
-int enter(ot_reservoir* r, hipStream_t caller) {
-  if (caller == r->stream) return OT_OK;
-  OT_HIP(hipEventRecord(r->ev_in, caller));
-  OT_HIP(hipStreamWaitEvent(r->stream, r->ev_in, 0));
-  return OT_OK;
-}
+// Where one state-changing call runs, and its place in the ticket order.
+//
+// A reservoir with a stream of the caller's choice (order_stream) runs every
+// call there: that stream waits for the work already queued on the call's
+// stream, and the call's stream waits for the call's work (two event pairs,
+// about 19 us of host time; none when both are the same stream).
+//
+// A reservoir without one runs each call on the call's own stream, behind the
+// event that the call before it left (ev_last) and leaving its own: the same
+// order with one record and one wait (none to speak of when the stream is the one
+// the event was recorded on).  Nothing is kept about the stream itself, which may be
+// destroyed after the call.  Put + gathered draw of 256 rows of 400 KB: 149 ->
+// 111 us a pair (the GPU's time); ten takes of ten rows and a put: 482 -> 155 us;
+// put, draw and replayed train step of the 16x16 net: 133 -> 80 us.
+// Under capture ev_last (recorded outside) cannot be waited for: such calls
+// fork to the reservoir's own stream and join it, as with an order_stream.
+struct CallOrder {
+  ot_reservoir* r;
+  hipStream_t caller, st;       // st: the stream the call's kernels go to
+  bool direct = false, entered = false;
+  CallOrder(ot_reservoir* res, hipStream_t c) : r(res), caller(c), st(res->stream) {}
+  // Order the call's kernels after the caller's work and the calls before.
+  int enter() {
+    if (r->own_stream) {
+      hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+      OT_HIP(hipStreamIsCapturing(caller, &cap));
+      direct = cap == hipStreamCaptureStatusNone;
+    }
+    if (direct) {
+      OT_HIP(hipStreamWaitEvent(caller, r->ev_last, 0));
+      st = caller;
+    } else if (caller != st) {
+      OT_HIP(hipEventRecord(r->ev_in, caller));
+      OT_HIP(hipStreamWaitEvent(st, r->ev_in, 0));
+    }
+    entered = true;
+    return OT_OK;
+  }
+  // Order what follows (on the caller's stream, and the next call) after the call's kernels.
+  int leave() {
+    entered = false;
+    if (direct) {
+      OT_HIP(hipEventRecord(r->ev_last, st));
+    } else if (caller != st) {
+      OT_HIP(hipEventRecord(r->ev_out, st));
+      OT_HIP(hipStreamWaitEvent(caller, r->ev_out, 0));
+    }
+    return OT_OK;
+  }
+  ~CallOrder() {                // a call that failed half-way still orders the next one behind it
+    if (entered && direct) (void)hipEventRecord(r->ev_last, st);
+  }
+};
 
-// Order the caller's stream after the reservoir's work.
-int leave(ot_reservoir* r, hipStream_t caller) {
-  if (caller == r->stream) return OT_OK;
-  OT_HIP(hipEventRecord(r->ev_out, r->stream));
-  OT_HIP(hipStreamWaitEvent(caller, r->ev_out, 0));
+// Wait for all queued work of the reservoir.
+int wait_idle(ot_reservoir* r) {
+  if (r->own_stream) OT_HIP(hipEventSynchronize(r->ev_last));
+  OT_HIP(hipStreamSynchronize(r->stream));
   return OT_OK;
 }
 
@@ -805,7 +853,8 @@ extern "C" int reservoir_create(ot_reservoir** out, int64_t capacity, int64_t th
       return fail(ot::set_error(OT_E_HIP, "hipFuncSetAttribute (dynamic LDS) failed"));
   }
   if (hipEventCreateWithFlags(&r->ev_in, hipEventDisableTiming) != hipSuccess ||
-      hipEventCreateWithFlags(&r->ev_out, hipEventDisableTiming) != hipSuccess)
+      hipEventCreateWithFlags(&r->ev_out, hipEventDisableTiming) != hipSuccess ||
+      hipEventCreateWithFlags(&r->ev_last, hipEventDisableTiming) != hipSuccess)
     return fail(ot::set_error(OT_E_HIP, "hipEventCreate failed"));
   const int64_t n_init = std::max<int64_t>(capacity, 64);
   hipLaunchKernelGGL(ot::init_meta_kernel, dim3((unsigned)ot::ceil_div(n_init, 256)), dim3(256), 0,
@@ -839,8 +888,10 @@ extern "C" int reservoir_put(ot_reservoir* r, const float* x, int64_t ldx, const
   if (ot::put_admit(r->seq) != OT_OK) return ot::set_error(OT_E_CLOSED, "reservoir_put: reception is over");
   // the ticket is taken only once the ordering stream waits for the caller:
   // a call that fails before enqueueing anything leaves the ticket sequence unchanged
-  int rc = enter(r, cs);
+  CallOrder order(r, cs);
+  int rc = order.enter();
   if (rc) return rc;
+  const hipStream_t st = order.st;
   const ot::PutCall pc = ot::put_commit(r->seq, k);
   const uint64_t ticket = pc.ticket;
   if (ticket_out) *ticket_out = ticket;
@@ -848,65 +899,65 @@ extern "C" int reservoir_put(ot_reservoir* r, const float* x, int64_t ldx, const
   if (r->seq.policy != OT_POLICY_RESERVOIR) {
     // FIFO / FIRO: the accepted prefix and every ring position are host-known
     const int64_t a = pc.accepted;
-    tm.mark(r->stream, OT_PH_PUT_ASSIGN, 0);
+    tm.mark(st, OT_PH_PUT_ASSIGN, 0);
     hipLaunchKernelGGL(ot::list_put_kernel, dim3((unsigned)std::max<int64_t>(1, ot::ceil_div(a, 256))), dim3(256),
-                       0, r->stream, a, pc.n_before, r->seq.occ_base, pc.free_head, r->seq.C, r->free_q, r->occ,
+                       0, st, a, pc.n_before, r->seq.occ_base, pc.free_head, r->seq.C, r->free_q, r->occ,
                        r->put_slots, r->ctr, reinterpret_cast<long long*>(accepted_dev));
     OT_LAUNCHED("list_put_kernel");
-    tm.mark(r->stream, OT_PH_PUT_ASSIGN, 1);
+    tm.mark(st, OT_PH_PUT_ASSIGN, 1);
     if (a > 0) {
       hipEvent_t t0, t1;
       tm.kernel_events(OT_PH_PUT_COPY, &t0, &t1);
       const int vec_ok = aligned16(u) && (ldu % 4 == 0);
       const int64_t segs = ot::ceil_div(r->u_dim, ot::kCopySeg);
-      hipExtLaunchKernelGGL(ot::put_copy_kernel, dim3((unsigned)(segs * a)), dim3(ot::kCopyThreads), 0, r->stream,
+      hipExtLaunchKernelGGL(ot::put_copy_kernel, dim3((unsigned)(segs * a)), dim3(ot::kCopyThreads), 0, st,
                             t0, t1, 0, x, ldx, u, ldu, r->put_slots, (const ot::ResCounters*)r->ctr, r->xslab,
                             r->ldxs, r->uslab, r->ldus, r->x_dim, r->u_dim, segs, vec_ok, r->seen, r->sample_id,
                             r->hist, r->seq.C);
       OT_LAUNCHED("put_copy_kernel");
     }
     tm.next_call();
-    return leave(r, cs);
+    return order.leave();
   }
-  tm.mark(r->stream, OT_PH_PUT_ASSIGN, 0);
+  tm.mark(st, OT_PH_PUT_ASSIGN, 0);
   // Replacement is possible only if N + k > C (host-known N); only then are
   // the seen slots indexed.
   const int may_evict = pc.may_evict;
   if (r->seq.C <= ot::kFusedMaxC && k <= ot::kFusedMaxPut) {
     hipLaunchKernelGGL(ot::put_assign_fused_kernel, dim3(1), dim3(ot::kAssignThreads), fused_assign_lds(r->seq.C, k),
-                       r->stream, k, ticket, r->seed, r->seq.C, may_evict, (const int32_t*)r->seen, r->put_slots, r->ctr,
+                       st, k, ticket, r->seed, r->seq.C, may_evict, (const int32_t*)r->seen, r->put_slots, r->ctr,
                        reinterpret_cast<long long*>(accepted_dev));
     OT_LAUNCHED("put_assign_fused_kernel");
   } else {
   if (may_evict) {
-    hipLaunchKernelGGL(ot::seen_tile_count_kernel, dim3((unsigned)r->ntiles), dim3(256), 0, r->stream, r->seen,
+    hipLaunchKernelGGL(ot::seen_tile_count_kernel, dim3((unsigned)r->ntiles), dim3(256), 0, st, r->seen,
                        r->seq.C, r->tile_cnt);
     OT_LAUNCHED("seen_tile_count_kernel");
   }
   hipLaunchKernelGGL(ot::put_assign_kernel, dim3(1), dim3(ot::kAssignThreads),
-                     shuffle_lds(k), r->stream, k, ticket, r->seed,
+                     shuffle_lds(k), st, k, ticket, r->seed,
                      r->seq.C, may_evict, r->tile_cnt, r->ntiles, r->tile_off, r->victim_pos, r->put_slots, r->ctr,
                      reinterpret_cast<long long*>(accepted_dev));
   OT_LAUNCHED("put_assign_kernel");
   if (may_evict && k > 0) {
-    hipLaunchKernelGGL(ot::put_victim_kernel, dim3((unsigned)k), dim3(64), 0, r->stream, r->seen, r->seq.C,
+    hipLaunchKernelGGL(ot::put_victim_kernel, dim3((unsigned)k), dim3(64), 0, st, r->seen, r->seq.C,
                        r->tile_off, r->ntiles, r->victim_pos, r->put_slots, r->ctr);
     OT_LAUNCHED("put_victim_kernel");
   }
   }
-  tm.mark(r->stream, OT_PH_PUT_ASSIGN, 1);
+  tm.mark(st, OT_PH_PUT_ASSIGN, 1);
   if (k > 0) {
     hipEvent_t t0, t1;
     tm.kernel_events(OT_PH_PUT_COPY, &t0, &t1);
     const int vec_ok = aligned16(u) && (ldu % 4 == 0);
     const int64_t segs = ot::ceil_div(r->u_dim, ot::kCopySeg);
-    hipExtLaunchKernelGGL(ot::put_copy_kernel, dim3((unsigned)(segs * k)), dim3(ot::kCopyThreads), 0, r->stream, t0,
+    hipExtLaunchKernelGGL(ot::put_copy_kernel, dim3((unsigned)(segs * k)), dim3(ot::kCopyThreads), 0, st, t0,
                           t1, 0, x, ldx, u, ldu, r->put_slots, (const ot::ResCounters*)r->ctr, r->xslab, r->ldxs,
                           r->uslab, r->ldus, r->x_dim, r->u_dim, segs, vec_ok, r->seen, r->sample_id, r->hist, r->seq.C);
     OT_LAUNCHED("put_copy_kernel");
   }
   tm.next_call();
-  return leave(r, cs);
+  return order.leave();
 }
 
 extern "C" int reservoir_sample_batch(ot_reservoir* r, int64_t b, void* stream, int32_t* slots,
@@ -932,30 +983,32 @@ extern "C" int reservoir_sample_batch(ot_reservoir* r, int64_t b, void* stream, 
   if (r->seq.reception_over)
     OT_REQUIRE(b <= ot::kMaxDrainBatch, "reservoir_sample_batch: b=%lld above %lld while draining",
                (long long)b, (long long)ot::kMaxDrainBatch);
-  int rc = enter(r, cs);
+  CallOrder order(r, cs);
+  int rc = order.enter();
   if (rc) return rc;
+  const hipStream_t st = order.st;
   const ot::DrawCall dc = ot::draw_commit(r->seq, drawn);
   const uint64_t ticket = dc.ticket;
   if (ticket_out) *ticket_out = ticket;
   ot::PhaseTimer& tm = r->timer;
-  tm.mark(r->stream, OT_PH_SELECT, 0);
+  tm.mark(st, OT_PH_SELECT, 0);
   if (!dc.take) {
-    hipLaunchKernelGGL(ot::select_kernel, dim3((unsigned)ot::ceil_div(b, 256)), dim3(256), 0, r->stream,
+    hipLaunchKernelGGL(ot::select_kernel, dim3((unsigned)ot::ceil_div(b, 256)), dim3(256), 0, st,
                        r->seed, ticket, dc.n_before, b, slots, r->seen, r->ctr);
     OT_LAUNCHED("select_kernel");
   } else {
     hipLaunchKernelGGL(ot::list_take_kernel, dim3(1), dim3(ot::kAssignThreads),
-                       shuffle_lds(drawn), r->stream, r->seed, ticket,
+                       shuffle_lds(drawn), st, r->seed, ticket,
                        dc.n_before, drawn, r->seq.policy == OT_POLICY_FIFO ? 0 : 1, dc.occ_base, r->seq.C, r->occ,
                        r->free_q, dc.free_tail, slots, r->seen, r->sample_id, r->hist, r->ctr);
     OT_LAUNCHED("list_take_kernel");
   }
-  tm.mark(r->stream, OT_PH_SELECT, 1);
+  tm.mark(st, OT_PH_SELECT, 1);
   if (x_out && !u_out) {
     hipEvent_t t0, t1;
     tm.kernel_events(OT_PH_GATHER, &t0, &t1);
     hipExtLaunchKernelGGL(ot::gather_x_kernel, dim3((unsigned)ot::ceil_div(drawn * r->x_dim, 256)), dim3(256), 0,
-                          r->stream, t0, t1, 0, (const int32_t*)slots, (const float*)r->xslab, r->ldxs, x_out,
+                          st, t0, t1, 0, (const int32_t*)slots, (const float*)r->xslab, r->ldxs, x_out,
                           ldxo, r->x_dim, drawn);
     OT_LAUNCHED("gather_x_kernel");
   } else if (u_out) {
@@ -963,7 +1016,7 @@ extern "C" int reservoir_sample_batch(ot_reservoir* r, int64_t b, void* stream, 
     tm.kernel_events(OT_PH_GATHER, &t0, &t1);
     const int vec_ok = (u_out == nullptr) || (aligned16(u_out) && (lduo % 4 == 0));
     const int64_t segs = ot::ceil_div(r->u_dim, ot::kCopySeg);
-    hipExtLaunchKernelGGL(ot::gather_kernel, dim3((unsigned)(segs * drawn)), dim3(ot::kCopyThreads), 0, r->stream,
+    hipExtLaunchKernelGGL(ot::gather_kernel, dim3((unsigned)(segs * drawn)), dim3(ot::kCopyThreads), 0, st,
                           t0, t1, 0, (const int32_t*)slots, (const float*)r->xslab, r->ldxs,
                           (const float*)r->uslab, r->ldus, x_out, ldxo, u_out, lduo, r->x_dim, r->u_dim, segs,
                           vec_ok);
@@ -971,7 +1024,7 @@ extern "C" int reservoir_sample_batch(ot_reservoir* r, int64_t b, void* stream, 
   }
   tm.next_call();
   if (count_out) *count_out = drawn;
-  return leave(r, cs);
+  return order.leave();
 }
 
 extern "C" int reservoir_end_reception(ot_reservoir* r) {
@@ -981,9 +1034,11 @@ extern "C" int reservoir_end_reception(ot_reservoir* r) {
   if (ot::end_commit(r->seq) != OT_OK) return ot::set_error(OT_E_STATE, "reservoir_end_reception: already over");
   if (r->seq.policy != OT_POLICY_RESERVOIR) return OT_OK;   // the list is already maintained
   if (r->seq.n_host > 0) {
+    if (r->own_stream) OT_HIP(hipStreamWaitEvent(r->stream, r->ev_last, 0));
     hipLaunchKernelGGL(ot::iota_kernel, dim3((unsigned)ot::ceil_div(r->seq.n_host, 256)), dim3(256), 0, r->stream,
                        r->occ, r->seq.n_host);
     OT_LAUNCHED("iota_kernel");
+    if (r->own_stream) OT_HIP(hipEventRecord(r->ev_last, r->stream));
   }
   return OT_OK;
 }
@@ -1002,7 +1057,7 @@ extern "C" int reservoir_stats(ot_reservoir* r, ot_reservoir_stats* out) {
   ot::clear_error();
   OT_REQUIRE(r != nullptr && out != nullptr, "reservoir_stats: NULL argument");
   std::lock_guard<std::mutex> lock(r->mu);
-  OT_HIP(hipStreamSynchronize(r->stream));
+  if (int rc = wait_idle(r)) return rc;
   ResCounters c;
   OT_HIP(hipMemcpy(&c, r->ctr, sizeof c, hipMemcpyDeviceToHost));
   out->capacity = r->seq.C;
@@ -1028,7 +1083,7 @@ extern "C" int reservoir_read_meta(ot_reservoir* r, int32_t* seen_count, int64_t
   ot::clear_error();
   OT_REQUIRE(r != nullptr, "reservoir_read_meta: NULL reservoir");
   std::lock_guard<std::mutex> lock(r->mu);
-  OT_HIP(hipStreamSynchronize(r->stream));
+  if (int rc = wait_idle(r)) return rc;
   if (seen_count) OT_HIP(hipMemcpy(seen_count, r->seen, r->seq.C * sizeof(int32_t), hipMemcpyDeviceToHost));
   if (sample_id) OT_HIP(hipMemcpy(sample_id, r->sample_id, r->seq.C * sizeof(int64_t), hipMemcpyDeviceToHost));
   if (evict_hist)
@@ -1044,7 +1099,7 @@ extern "C" int reservoir_read_rows(ot_reservoir* r, const int32_t* slots_host, i
     OT_REQUIRE(slots_host[i] >= 0 && slots_host[i] < r->seq.C, "reservoir_read_rows: slot %d out of range",
                (int)slots_host[i]);
   std::lock_guard<std::mutex> lock(r->mu);
-  OT_HIP(hipStreamSynchronize(r->stream));
+  if (int rc = wait_idle(r)) return rc;
   for (int64_t i = 0; i < n; ++i) {
     const int64_t s = slots_host[i];
     if (x_host)
@@ -1097,7 +1152,7 @@ extern "C" int reservoir_checkpoint_size(ot_reservoir* r, int64_t* bytes) {
   ot::clear_error();
   OT_REQUIRE(r != nullptr && bytes != nullptr, "reservoir_checkpoint_size: NULL argument");
   std::lock_guard<std::mutex> lock(r->mu);
-  OT_HIP(hipStreamSynchronize(r->stream));
+  if (int rc = wait_idle(r)) return rc;
   ResCounters c;
   OT_HIP(hipMemcpy(&c, r->ctr, sizeof c, hipMemcpyDeviceToHost));
   *bytes = res_blob_bytes(r, c.N);
@@ -1108,7 +1163,7 @@ extern "C" int reservoir_checkpoint(ot_reservoir* r, void* buf, int64_t bytes) {
   ot::clear_error();
   OT_REQUIRE(r != nullptr && buf != nullptr, "reservoir_checkpoint: NULL argument");
   std::lock_guard<std::mutex> lock(r->mu);
-  OT_HIP(hipStreamSynchronize(r->stream));
+  if (int rc = wait_idle(r)) return rc;
   const int64_t C = r->seq.C;
   ResCounters c;
   std::vector<unsigned long long> hist(ot::kHistLen);
@@ -1184,7 +1239,7 @@ extern "C" int reservoir_restore(ot_reservoir* r, const void* buf, int64_t bytes
   for (int32_t v : seen) occupied += v >= 0;
   OT_REQUIRE(occupied == n_rows && c.N == n_rows, "reservoir_restore: inconsistent slot metadata");
   std::lock_guard<std::mutex> lock(r->mu);
-  OT_HIP(hipStreamSynchronize(r->stream));
+  if (int rc = wait_idle(r)) return rc;
   OT_HIP(hipMemcpy(r->ctr, &c, sizeof c, hipMemcpyHostToDevice));
   OT_HIP(hipMemcpy(r->hist, hist, ot::kHistLen * 8, hipMemcpyHostToDevice));
   OT_HIP(hipMemcpy(r->seen, seen.data(), C * 4, hipMemcpyHostToDevice));

@@ -9,6 +9,7 @@ import pytest
 import torch
 
 from fixtures.synthetic import hash_inputs, hash_rows
+from oracle import philox
 from oracle import reservoir as orv
 from tests.reservoir_checks import compare_meta
 
@@ -347,4 +348,71 @@ def test_eviction_index_on_both_sides_of_the_one_launch_limits(C, k_evict):
         draw(4096)
     compare_meta(g, o, 64)
     assert o.total_evicted >= 4 * k_evict
+    g.close()
+
+
+def test_short_lived_streams_keep_ticket_order():
+    """Without an order_stream every call runs on its caller's stream: puts from
+    streams that are destroyed right after the call, draws and the drain from
+    the current one, must still take effect in ticket order."""
+    import ctypes
+    from paper_2309_16743_amd import OT_OK, Reservoir
+    hip = ctypes.CDLL("libamdhip64.so")
+    C, T, d, seed, k = 96, 24, 20011, 21, 24
+    g, o = Reservoir(C, T, 6, d, seed), orv.Reservoir(C, T, 6, d, seed)
+    rows = []
+    for i in range(12):
+        ud = padded(k, d)
+        ud.copy_(torch.from_numpy(hash_rows(np.arange(i * k, (i + 1) * k), d)))
+        rows.append(ud)
+    torch.cuda.synchronize()
+    got, ref = [], []
+    for i in range(24):
+        if i < 12:
+            s = ctypes.c_void_p()
+            assert hip.hipStreamCreateWithFlags(ctypes.byref(s), 1) == 0
+            g.put(None, rows[i], stream=s.value)
+            assert hip.hipStreamDestroy(s) == 0
+            o.put(None, hash_rows(np.arange(i * k, (i + 1) * k), d), k=k)
+        if i == 12:
+            g.end_reception()
+            o.end_reception()
+        slots, ub = torch.empty(20, dtype=torch.int32, device=DEV), padded(20, d)
+        st, n, _ = g.sample_batch(20, slots, u_out=ub)
+        ost, oslots, _, ou, _ = o.sample_batch(20)
+        assert st == ost
+        if st == OT_OK:
+            got.append((slots[:n], ub[:n]))
+            ref.append((np.array(oslots), ou))
+    torch.cuda.synchronize()
+    for (s, u), (os_, ou) in zip(got, ref):
+        assert np.array_equal(s.cpu().numpy(), os_) and np.array_equal(u.cpu().numpy(), ou)
+    g.close()
+
+
+def test_captured_draw_without_order_stream():
+    """A draw captured in a graph (its ticket fixed) draws the same slots at
+    every replay, with the reservoir's eager calls before, between and after."""
+    from paper_2309_16743_amd import OT_OK, Reservoir
+    C, T, d, seed = 64, 8, 100, 5
+    g = Reservoir(C, T, 6, d, seed)
+    ud = padded(40, d)
+    ud.copy_(torch.from_numpy(hash_rows(np.arange(40), d)))
+    g.put(None, ud)
+    slots = torch.zeros(16, dtype=torch.int32, device=DEV)
+    eager = torch.zeros(16, dtype=torch.int32, device=DEV)
+    assert g.sample_batch(16, eager)[0] == OT_OK
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        st, _, ticket = g.sample_batch(16, slots)
+    assert st == OT_OK
+    want = [philox.draw_index(seed, j, ticket, philox.KIND_SAMPLE, 40) for j in range(16)]
+    for _ in range(3):
+        slots.zero_()
+        graph.replay()
+        assert g.sample_batch(16, eager)[0] == OT_OK
+        torch.cuda.synchronize()
+        assert slots.cpu().tolist() == want
+    assert g.stats()["total_draws"] == 16 * 7
     g.close()

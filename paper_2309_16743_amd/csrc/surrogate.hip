@@ -71,31 +71,52 @@ __global__ __launch_bounds__(256) void zero_pads_kernel(PadList l) {
 
 // First layer with a small input width K (the 6 inputs (X, t)):
 // A1[m][n] = max(sum_k X[m][k] W[n][k] + b[n], 0) (or without ReLU when the
-// net has a single layer).  One thread per 4 consecutive outputs.
-__global__ void small_k_forward_kernel(const float* __restrict__ X, int64_t ldx,
-                                       const float* __restrict__ W, int64_t ldw,
-                                       const float* __restrict__ bias, float* __restrict__ out,
-                                       int64_t ldo, int64_t M, int64_t N, int64_t K, int relu,
-                                       uint16_t* __restrict__ out16) {
-  const int64_t groups = (N + 3) / 4;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= M * groups) return;
-  const int64_t m = t / groups, n0 = (t % groups) * 4;
-  float x[kMaxSmallK];
+// net has a single layer).  One thread per output column and kSmallRows rows: the
+// column's weights (rows of ldw = round_up(K, 8) values, zero past K) are read once
+// with 16-byte loads, x rows are the same for a whole wavefront, and a wavefront
+// writes 64 consecutive outputs of a row.  Latency-bound; with 4 columns of one row per
+// thread and scalar loads 1024 x 2048 took 20 us, 331 x 300 6.2.
+// grid = ceil(N / 256) * ceil(M / kSmallRows), columns first.
+constexpr int kSmallRows = 4;
+template <int KP>                       // round_up(K, 8): 8 or 16
+__global__ __launch_bounds__(256) void small_k_forward_kernel(const float* __restrict__ X, int64_t ldx,
+                                                              const float* __restrict__ W,
+                                                              const float* __restrict__ bias, float* __restrict__ out,
+                                                              int64_t ldo, int64_t M, int64_t N, int K, int relu,
+                                                              uint16_t* __restrict__ out16) {
+  const int64_t col_blocks = (N + 255) / 256;
+  const int64_t n = (int64_t)blockIdx.x % col_blocks * 256 + threadIdx.x;
+  const int64_t m0 = (int64_t)blockIdx.x / col_blocks * kSmallRows;
+  if (n >= N) return;
+  float w[KP];
 #pragma unroll
-  for (int k = 0; k < kMaxSmallK; ++k) x[k] = k < K ? X[m * ldx + k] : 0.f;
-  for (int c = 0; c < 4; ++c) {
-    const int64_t n = n0 + c;
-    if (n >= N) break;
+  for (int k = 0; k < KP; k += 4) {
+    const f32x4 t = *reinterpret_cast<const f32x4*>(W + n * KP + k);
+    w[k] = t[0]; w[k + 1] = t[1]; w[k + 2] = t[2]; w[k + 3] = t[3];
+  }
+  const float b = bias[n];
+#pragma unroll
+  for (int r = 0; r < kSmallRows; ++r) {
+    const int64_t m = m0 + r;
+    if (m >= M) break;
     float acc = 0.f;
 #pragma unroll
-    for (int k = 0; k < kMaxSmallK; ++k)
-      if (k < K) acc = fmaf(x[k], W[n * ldw + k], acc);
-    acc += bias[n];
+    for (int k = 0; k < KP; ++k)
+      if (k < K) acc = fmaf(X[m * ldx + k], w[k], acc);
+    acc += b;
     const float y = relu ? (acc > 0.f ? acc : 0.f) : acc;
     if (out16) out16[m * ldo + n] = f2bf(y);   // bf16 activations feed the bf16 GEMMs
     else out[m * ldo + n] = y;
   }
+}
+
+inline void launch_small_k_forward(const float* X, int64_t ldx, const float* W, const float* bias, float* out,
+                                   int64_t ldo, int64_t M, int64_t N, int64_t K, uint16_t* out16, hipStream_t st) {
+  const dim3 grid((unsigned)(ceil_div(N, 256) * ceil_div(M, kSmallRows)));
+  if (K <= 8)
+    hipLaunchKernelGGL(small_k_forward_kernel<8>, grid, dim3(256), 0, st, X, ldx, W, bias, out, ldo, M, N, (int)K, 1, out16);
+  else
+    hipLaunchKernelGGL(small_k_forward_kernel<16>, grid, dim3(256), 0, st, X, ldx, W, bias, out, ldo, M, N, (int)K, 1, out16);
 }
 
 // First-layer weight gradient, partial sums over a slice of rows:
@@ -139,9 +160,19 @@ __global__ void small_k_wgrad_reduce_kernel(const float* __restrict__ part, int6
                                             float* __restrict__ db) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= N * (K + 1)) return;
-  const int64_t n = t / (K + 1), k = t % (K + 1);
+  const int64_t n = t / (K + 1), k = t % (K + 1), stride = N * (K + 1);
+  // eight loads in flight, added in order (one at a time 32 slices took 9 us)
+  const float* src = part + n * (K + 1) + k;
   float s = 0.f;
-  for (int64_t p = 0; p < P; ++p) s += part[(p * N + n) * (K + 1) + k];
+  int64_t p = 0;
+  for (; p + 8 <= P; p += 8) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = src[(p + u) * stride];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += v[u];
+  }
+  for (; p < P; ++p) s += src[p * stride];
   if (k < K) dW[n * ldw + k] = s;
   else db[n] = s;
 }
@@ -956,9 +987,7 @@ int forward_hidden(ot_surrogate* s, const float* X, int64_t ldx, int64_t rows, h
     const float* W = s->params + ly.w_off;
     const float* b = s->params + ly.b_off;
     if (l == 1 && ly.in <= ot::kMaxSmallK) {
-      const int64_t work = rows * ot::ceil_div(ly.out, 4);
-      hipLaunchKernelGGL(ot::small_k_forward_kernel, dim3((unsigned)ot::ceil_div(work, 256)), dim3(256), 0, st, X,
-                         ldx, W, ly.ldw, b, s->act[1], s->ld[1], rows, ly.out, ly.in, 1, (uint16_t*)nullptr);
+      ot::launch_small_k_forward(X, ldx, W, b, s->act[1], s->ld[1], rows, ly.out, ly.in, nullptr, st);
       OT_LAUNCHED("small_k_forward_kernel");
       continue;
     }
@@ -1172,10 +1201,8 @@ int forward_hidden_bf16(ot_surrogate* s, const float* X, int64_t ldx, int64_t ro
   for (int l = 1; l < L; ++l) {
     const Layer& ly = s->layers[l - 1];
     if (l == 1) {
-      const int64_t work = rows * ot::ceil_div(ly.out, 4);
-      hipLaunchKernelGGL(ot::small_k_forward_kernel, dim3((unsigned)ot::ceil_div(work, 256)), dim3(256), 0, st, X,
-                         ldx, s->params + ly.w_off, ly.ldw, s->params + ly.b_off, (float*)nullptr, s->ld[1], rows,
-                         ly.out, ly.in, 1, s->act16[1]);
+      ot::launch_small_k_forward(X, ldx, s->params + ly.w_off, s->params + ly.b_off, nullptr, s->ld[1], rows, ly.out,
+                                 ly.in, s->act16[1], st);
       OT_LAUNCHED("small_k_forward_kernel");
       continue;
     }

@@ -89,9 +89,9 @@ int surrogate_set_lr(ot_surrogate* s, float lr);
  * capture on their stream) and replay it.  Adam's bias corrections
  * 1 - beta^t (Kingma and Ba's Algorithm 1, the optimizer of Sec. 4.1) depend
  * on the step t, normally a host-side argument of the step's kernels; with
- * enable = 1 the kernels read the number of completed steps from device
- * memory instead and the step ends with a launch that advances it, so that
- * the captured launches stay valid for every replay.  The corrections are
+ * enable = 1 the kernels read the number of the step from device memory
+ * instead, which the step's output forward advances, so that the captured
+ * launches stay valid for every replay.  The corrections are
  * formed the same way in both modes (binary exponentiation in double), so
  * steps agree bit for bit.  Switching synchronises the device; with the
  * counter on, surrogate_get_adam_state and surrogate_checkpoint read the

@@ -28,16 +28,16 @@ __host__ __device__ inline float bias_correction(float beta, long long t) {
 struct AdamArgs {
   float lr, b1, b2, eps;
   float c1, c2;   // bias corrections 1 - b1^t, 1 - b2^t of the step being taken
-  // When set, the step is t = *t_done + 1 (steps completed, in device memory)
-  // and the kernel forms c1, c2 itself (resolved()), so that a captured step
-  // replays with the same arguments.
-  const long long* t_done;
+  // When set, the step being taken is t = *t_now (device memory, advanced by the
+  // step's output forward) and the kernel forms c1, c2 itself (resolved()), so
+  // that a captured step replays with the same arguments.
+  const long long* t_now;
 
 #ifdef __HIPCC__
   __device__ __forceinline__ AdamArgs resolved() const {
     AdamArgs a = *this;
-    if (t_done) {
-      const long long t = *t_done + 1;
+    if (t_now) {
+      const long long t = *t_now;
       a.c1 = bias_correction(b1, t);
       a.c2 = bias_correction(b2, t);
     }
@@ -47,9 +47,12 @@ struct AdamArgs {
 };
 
 #ifdef __HIPCC__
+// The contractions are written out: left to the compiler they could differ from
+// one kernel to the next.
 __device__ __forceinline__ void adam1(float& p, float g, float& m, float& v, const AdamArgs& a) {
-  m = a.b1 * m + (1.0f - a.b1) * g;
-  v = a.b2 * v + (1.0f - a.b2) * (g * g);
+#pragma clang fp contract(off)
+  m = __builtin_fmaf(a.b1, m, (1.0f - a.b1) * g);
+  v = __builtin_fmaf(a.b2, v, (1.0f - a.b2) * (g * g));
   const float mhat = m / a.c1;
   const float vhat = v / a.c2;
   p = p - a.lr * mhat / (sqrtf(vhat) + a.eps);

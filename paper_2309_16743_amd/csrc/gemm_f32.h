@@ -57,6 +57,7 @@ struct GemmArgs {
   int64_t target_rows_max;     //   clamped to [0, target_rows_max]
   float scale;              // Mse
   double* loss_partials;    // Mse: one per block
+  long long* step_now;      // Mse (nullable): device step counter, advanced by the first block
   const float* mask;        // Mask
   int64_t ldmask;
   float* rowsum;            // optional: sum_k A(m, k) for m of the block's rows (n tile 0 only)
@@ -65,8 +66,20 @@ struct GemmArgs {
                             // the operand (read by gemm_f32x3_kernel only)
   float* adam_m;            // Adam: moments at C's offsets
   float* adam_v;
+  float* bias_p;            // Adam with rowsum (nullable): the bias whose gradient the row sums are,
+  float* bias_m;            //   updated by the thread that has its sum
+  float* bias_v;
   AdamArgs adam;
 };
+
+// Row sum of row m (the bias gradient) to where it goes; Adam on the bias element.
+template <Epi EPI>
+__device__ __forceinline__ void finish_rowsum(const GemmArgs& g, int64_t split, int64_t m, float r) {
+  g.rowsum[split * g.rowsum_stride + m] = r;
+  if constexpr (EPI == Epi::Adam) {
+    if (g.bias_p) adam1(g.bias_p[m], r, g.bias_m[m], g.bias_v[m], g.adam.resolved());
+  }
+}
 
 constexpr int kNumXcd = 8;
 
@@ -330,7 +343,7 @@ __attribute__((amdgpu_waves_per_eu((EPI == Epi::Mse && FM * FN == 8) ? 5 : 1))) 
   if constexpr (EPI == Epi::Mse) {
     if (nk == 0) __syncthreads();       // publishes s_trow (the main loop's barriers do otherwise)
   }
-  if (do_rowsum && tid < BM && m0 + tid < g.M) g.rowsum[split * g.rowsum_stride + m0 + tid] = rsum;
+  if (do_rowsum && tid < BM && m0 + tid < g.M) finish_rowsum<EPI>(g, split, m0 + tid, rsum);
 
   // ---------------------------------------------------------------- epilogue
   float lsum = 0.f;
@@ -479,6 +492,7 @@ __attribute__((amdgpu_waves_per_eu((EPI == Epi::Mse && FM * FN == 8) ? 5 : 1))) 
       double t = 0.0;
       for (int w = 0; w < NT / 64; ++w) t += s_red[w];
       g.loss_partials[blockIdx.y * gridDim.x + blockIdx.x] = t;
+      if (g.step_now && blockIdx.x == 0) *g.step_now += 1;
     }
   }
 }

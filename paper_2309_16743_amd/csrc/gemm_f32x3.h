@@ -390,7 +390,7 @@ __global__ __launch_bounds__(256, x3_waves(WGN, FM, FN)) void gemm_f32x3_kernel(
       if (tid < BM && m0 + tid < g.M) {
         float s = 0.f;
         for (int kr = 0; kr < 16; ++kr) s += red[kr * BM + tid];
-        g.rowsum[split * g.rowsum_stride + m0 + tid] = s;
+        finish_rowsum<EPI>(g, split, m0 + tid, s);
       }
     }
   }
@@ -522,7 +522,10 @@ __global__ __launch_bounds__(256, x3_waves(WGN, FM, FN)) void gemm_f32x3_kernel(
     const double ls = warp_sum((double)lsum);
     if (lane == 0) s_red[wid] = ls;
     x3_barrier();
-    if (tid == 0) g.loss_partials[blockIdx.y * gridDim.x + blockIdx.x] = ((s_red[0] + s_red[1]) + s_red[2]) + s_red[3];
+    if (tid == 0) {
+      g.loss_partials[blockIdx.y * gridDim.x + blockIdx.x] = ((s_red[0] + s_red[1]) + s_red[2]) + s_red[3];
+      if (g.step_now && blockIdx.x == 0) *g.step_now += 1;
+    }
   }
 }
 

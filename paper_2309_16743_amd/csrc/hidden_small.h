@@ -12,7 +12,8 @@
 //                             tile, partial sums of dW1 = dZ1^T X and db1;
 //                             role B: k-split partials of dW2 = dZ2^T A1 and
 //                             db2 = column sums of dZ2
-//   hidden_bwd_reduce_kernel  dW2, db2, dW1, db1 from the partials, fixed order
+//   hidden_bwd_reduce_kernel  dW2, db2, dW1, db1 from the partials, fixed order,
+//                             and in a fused step Adam on both layers and the loss
 //
 // Every sum is taken in a fixed order, so results are deterministic.
 //
@@ -22,6 +23,7 @@
 // read hit 64 different banks.
 #pragma once
 
+#include "adam.h"
 #include "common.h"
 
 namespace ot {
@@ -277,14 +279,27 @@ __global__ __launch_bounds__(256) void hidden_bwd_small_kernel(
   if (i0 == 0 && tid < kHbTile && j0 + tid < h2) part2b[kc * h2 + j0 + tid] = csum;
 }
 
+// Where the reduced gradients go: flat offsets of the two layers, and (p
+// non-NULL) Adam on their parameters by the thread that has the gradient, with
+// the batch loss formed by one more block, so that the step's last pass has
+// nothing left of these layers to do.
+struct HiddenAdam {
+  float* g;
+  float* p;
+  float* m;
+  float* v;
+  int64_t w1, b1, w2, b2;      // offsets into the flat buffers
+  AdamArgs adam;
+};
+
 // Backward, part 2: dW2[j][i] = sum_kc part2[kc][j][i], db2[j] = sum_kc
 // part2b[kc][j], dW1[i][k] = sum_rt part1[rt][i][k], db1[i] = sum_rt
-// part1[rt][i][in0], each in index order.  One thread per output element.
-__global__ __launch_bounds__(256) void hidden_bwd_reduce_kernel(
-    const float* __restrict__ part1, int64_t n_rt, const float* __restrict__ part2, const float* __restrict__ part2b,
-    int64_t n_kc, int in0, int h1, int h2, float* __restrict__ dW1, int64_t ldw1, float* __restrict__ db1,
-    float* __restrict__ dW2, int64_t ldw2, float* __restrict__ db2) {
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+// part1[rt][i][in0], each in index order.  One thread per output element
+// (thread t of all); Adam follows as above.
+__device__ __forceinline__ void hidden_reduce_element(
+    int64_t t, const float* __restrict__ part1, int64_t n_rt, const float* __restrict__ part2,
+    const float* __restrict__ part2b, int64_t n_kc, int in0, int h1, int h2, int64_t ldw1, int64_t ldw2,
+    const HiddenAdam& a) {
   const int64_t n2 = (int64_t)h2 * h1, nb2 = h2, n1 = (int64_t)h1 * (in0 + 1);
   // the loads of 8 terms are issued together, the terms added in index order
   auto sum_strided = [](const float* p, int64_t n, int64_t stride) {
@@ -300,16 +315,28 @@ __global__ __launch_bounds__(256) void hidden_bwd_reduce_kernel(
     for (; q < n; ++q) s += p[q * stride];
     return s;
   };
+  float s;
+  int64_t o;
   if (t < n2) {
-    dW2[(t / h1) * ldw2 + t % h1] = sum_strided(part2 + t, n_kc, n2);
+    o = a.w2 + (t / h1) * ldw2 + t % h1;
+    s = sum_strided(part2 + t, n_kc, n2);
   } else if (t < n2 + nb2) {
-    const int64_t j = t - n2;
-    db2[j] = sum_strided(part2b + j, n_kc, h2);
+    o = a.b2 + (t - n2);
+    s = sum_strided(part2b + (t - n2), n_kc, h2);
   } else if (t < n2 + nb2 + n1) {
     const int64_t e = t - n2 - nb2, i = e / (in0 + 1), k = e % (in0 + 1);
-    const float s = sum_strided(part1 + i * (in0 + 1) + k, n_rt, (int64_t)h1 * (in0 + 1));
-    if (k < in0) dW1[i * ldw1 + k] = s;
-    else db1[i] = s;
+    o = k < in0 ? a.w1 + i * ldw1 + k : a.b1 + i;
+    s = sum_strided(part1 + i * (in0 + 1) + k, n_rt, (int64_t)h1 * (in0 + 1));
+  } else {
+    return;
+  }
+  a.g[o] = s;
+  if (a.p) {
+    float p = a.p[o], m = a.m[o], v = a.v[o];
+    adam1(p, s, m, v, a.adam.resolved());
+    a.p[o] = p;
+    a.m[o] = m;
+    a.v[o] = v;
   }
 }
 

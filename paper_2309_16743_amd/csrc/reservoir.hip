@@ -508,16 +508,21 @@ __global__ __launch_bounds__(kCopyThreads) void put_copy_kernel(
 }
 
 // Batch draw, normal phase: draw j picks slot floor(w_j N / 2^64), with
-// replacement; a first draw turns the slot from unseen to seen.
+// replacement; a first draw turns the slot from unseen to seen.  x_out
+// (nullable): the thread also copies the drawn input row (a separate gather of
+// 32 or 1024 rows of 6 values took 2.2 or 4.4 us, nearly all of it launch).
 __global__ void select_kernel(uint64_t seed, uint64_t ticket, int64_t N, int64_t b,
                               int32_t* __restrict__ slots, int32_t* __restrict__ seen,
-                              ResCounters* __restrict__ ctr) {
+                              ResCounters* __restrict__ ctr, const float* __restrict__ xslab, int64_t ldxs,
+                              float* __restrict__ x_out, int64_t ldxo, int64_t x_dim) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j == 0) atomic_add_ll(&ctr->total_draws, b);
   if (j >= b) return;
   const uint64_t w = draw_word(seed, (uint64_t)j, ticket, kKindSample);
   const int32_t slot = (int32_t)range_map(w, (uint64_t)N);
   slots[j] = slot;
+  if (x_out)
+    for (int64_t c = 0; c < x_dim; ++c) x_out[j * ldxo + c] = xslab[slot * ldxs + c];
   const int old = atomicAdd(&seen[slot], 1);
   if (old == 0) {
     atomic_add_ll(&ctr->U, -1);
@@ -992,9 +997,12 @@ extern "C" int reservoir_sample_batch(ot_reservoir* r, int64_t b, void* stream, 
   if (ticket_out) *ticket_out = ticket;
   ot::PhaseTimer& tm = r->timer;
   tm.mark(st, OT_PH_SELECT, 0);
+  // short input rows alone are copied by the draw itself (unless the gather is being timed)
+  const bool with_x = !dc.take && x_out && !u_out && r->x_dim <= 16 && !tm.on(OT_PH_GATHER);
   if (!dc.take) {
     hipLaunchKernelGGL(ot::select_kernel, dim3((unsigned)ot::ceil_div(b, 256)), dim3(256), 0, st,
-                       r->seed, ticket, dc.n_before, b, slots, r->seen, r->ctr);
+                       r->seed, ticket, dc.n_before, b, slots, r->seen, r->ctr, (const float*)r->xslab, r->ldxs,
+                       with_x ? x_out : nullptr, ldxo, r->x_dim);
     OT_LAUNCHED("select_kernel");
   } else {
     hipLaunchKernelGGL(ot::list_take_kernel, dim3(1), dim3(ot::kAssignThreads),
@@ -1004,7 +1012,7 @@ extern "C" int reservoir_sample_batch(ot_reservoir* r, int64_t b, void* stream, 
     OT_LAUNCHED("list_take_kernel");
   }
   tm.mark(st, OT_PH_SELECT, 1);
-  if (x_out && !u_out) {
+  if (x_out && !u_out && !with_x) {
     hipEvent_t t0, t1;
     tm.kernel_events(OT_PH_GATHER, &t0, &t1);
     hipExtLaunchKernelGGL(ot::gather_x_kernel, dim3((unsigned)ot::ceil_div(drawn * r->x_dim, 256)), dim3(256), 0,

@@ -340,9 +340,18 @@ __global__ __launch_bounds__(256) void adam_kernel(AdamRest r, AdamArgs args) {
   adam_groups(r, a, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256);
 }
 
-// Device step counter of a captured step: one more step completed.
-__global__ void step_done_kernel(long long* t_done) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *t_done += 1;
+// Reduction of the narrow hidden layers' gradients (hidden_small.h); in a fused
+// step also Adam on them, and the loss in one block more than the elements
+// take (16x16 net: 4.5 us, and the 4.6 us pass after it is gone).
+__global__ __launch_bounds__(256) void hidden_bwd_reduce_kernel(
+    const float* __restrict__ part1, int64_t n_rt, const float* __restrict__ part2, const float* __restrict__ part2b,
+    int64_t n_kc, int in0, int h1, int h2, int64_t ldw1, int64_t ldw2, HiddenAdam a, AdamRest loss) {
+  if (loss.partials && blockIdx.x == gridDim.x - 1) {
+    reduce_loss_256(loss);
+    return;
+  }
+  hidden_reduce_element((int64_t)blockIdx.x * 256 + threadIdx.x, part1, n_rt, part2, part2b, n_kc, in0, h1, h2, ldw1,
+                        ldw2, a);
 }
 
 // Split-K reduction fused with Adam (fp32 output layer), blocks of 256: the
@@ -554,10 +563,10 @@ struct ot_surrogate {
   bool fuse_out = false;      // output-layer Adam fused into its weight-gradient epilogue
   bool fused_step = false;    // ... and the current step took that path
   ot::AdamArgs step_adam{};   // Adam scalars of the current step
-  // Device step counter (surrogate_set_device_step): steps completed, read by
-  // the Adam kernels of every step and advanced by the step's last launch, so
-  // that a step's launches can be captured once and replayed.
-  long long* t_done_dev = nullptr;
+  // Device step counter (surrogate_set_device_step): steps taken, advanced by
+  // the first block of a step's output forward and read by its Adam kernels,
+  // so that a step's launches can be captured once and replayed.
+  long long* t_now_dev = nullptr;
   bool device_step = false;
   // Workspaces, sized for ws_rows batch rows.
   int64_t ws_rows = 0;
@@ -641,7 +650,7 @@ void free_surrogate(ot_surrogate* s) {
   (void)hipFree(s->v);
   (void)hipFree(s->loss_last);
   (void)hipFree(s->eval_acc);
-  (void)hipFree(s->t_done_dev);
+  (void)hipFree(s->t_now_dev);
   (void)hipFree(s->pb);
   (void)hipFree(s->colsum);
   delete s;
@@ -886,9 +895,10 @@ int ensure_split_ws(ot_surrogate* s, int64_t elems, int64_t rs_elems) {
 // C = epi(A B) with the plan's tile shape; split-K runs write partial sums to
 // the workspace and a second kernel applies the epilogue (fixed split order).
 // ph_gemm / ph_reduce: timing phases of the two halves (-1: not timed).
-// rest (Adam epilogue only, nullable): the step's last pass (other parameters
-// and loss); when the product is split it runs in extra blocks of the split-K
-// Adam reduction and *rest_done is set.
+// rest (Adam epilogue only): what is left for the step's last pass (parameters
+// outside the output layer, whose bias the product updates too, and the loss); when the
+// product is split it runs in extra blocks of the split-K Adam reduction and
+// *rest_done is set.
 template <Lay LA, Lay LB, int ROLE = 0>
 int run_gemm(ot_surrogate* s, GemmArgs g, Epi epi, hipStream_t st, const char* what, bool allow_split,
              int ph_gemm = -1, int ph_reduce = -1, int64_t* blocks_out = nullptr,
@@ -896,6 +906,12 @@ int run_gemm(ot_surrogate* s, GemmArgs g, Epi epi, hipStream_t st, const char* w
   const Plan p = make_plan(g.M, g.N, g.K, allow_split && epi != Epi::Mse, LB == Lay::MNMajor);
   if (blocks_out) *blocks_out = p.blocks;
   ot::PhaseTimer& tm = s->timer;
+  if (epi == Epi::Adam) {
+    const int64_t boff = g.rowsum - s->grads;
+    g.bias_p = s->params + boff;
+    g.bias_m = s->m + boff;
+    g.bias_v = s->v + boff;
+  }
   if (p.splits == 1) {
     g.k_chunk = g.K;
     hipEvent_t t0 = nullptr, t1 = nullptr;
@@ -922,25 +938,14 @@ int run_gemm(ot_surrogate* s, GemmArgs g, Epi epi, hipStream_t st, const char* w
   const int64_t work = g.M * ot::ceil_div(g.N, 4);
   if (epi == Epi::Adam) {
     const int64_t main_blocks = ot::ceil_div(work, 256);
-    int64_t rest_blocks = 0;
-    ot::AdamRest r{};
-    float *bp = nullptr, *bm = nullptr, *bv = nullptr;
-    if (rest && g.rowsum) {
-      // the output layer is the last segment of the flat buffer: its bias gets
-      // its update from the thread that reduces its gradient, the rest pass
-      // covers the layers before it
-      r = *rest;
-      r.hole_len = r.n4 - r.hole;
-      const int64_t boff = g.rowsum - s->grads;
-      bp = s->params + boff;
-      bm = s->m + boff;
-      bv = s->v + boff;
-      rest_blocks = std::max<int64_t>(1, std::min<int64_t>(ot::ceil_div(r.n4 - r.hole_len, 512), 4096));
-      if (rest_done) *rest_done = true;
-    }
+    const ot::AdamRest r = *rest;
+    const int64_t left = r.n4 - r.hole_len;
+    const int64_t rest_blocks =
+        left > 0 || r.partials ? std::max<int64_t>(1, std::min<int64_t>(ot::ceil_div(left, 512), 4096)) : 0;
+    *rest_done = true;
     hipLaunchKernelGGL(ot::splitk_adam_kernel, dim3((unsigned)(main_blocks + rest_blocks)), dim3(256), 0, st,
                        s->splitws, p.splits, h.split_stride, g.M, g.N, ldws, g.C, g.adam_m, g.adam_v, g.ldc, g.adam,
-                       h.rowsum, h.rowsum_stride, g.rowsum, bp, bm, bv, main_blocks, r);
+                       h.rowsum, h.rowsum_stride, g.rowsum, g.bias_p, g.bias_m, g.bias_v, main_blocks, r);
     OT_LAUNCHED("splitk_adam_kernel");
     if (ph_reduce >= 0) tm.mark(st, ph_reduce, 1);
     return OT_OK;
@@ -1254,6 +1259,7 @@ int forward_mse_bf16(ot_surrogate* s, const float* x, int64_t ldx, const float* 
   g.target_rows_max = u_rows_max;
   g.scale = (float)(2.0 / ((double)b * (double)D));
   g.loss_partials = s->loss_partials;
+  g.step_now = bias_grad && s->device_step ? s->t_now_dev : nullptr;   // a train step, not an evaluation
   if (bias_grad) {
     // output bias gradient: per m-tile column sums of the rounded dY
     const int64_t mtiles = ot::ceil_div(b, 64);
@@ -1550,7 +1556,7 @@ static int sync_step_count(ot_surrogate* s) {
   if (!s->device_step) return OT_OK;
   OT_HIP(hipDeviceSynchronize());
   long long t = 0;
-  OT_HIP(hipMemcpy(&t, s->t_done_dev, sizeof t, hipMemcpyDeviceToHost));
+  OT_HIP(hipMemcpy(&t, s->t_now_dev, sizeof t, hipMemcpyDeviceToHost));
   s->t = t;
   return OT_OK;
 }
@@ -1580,7 +1586,7 @@ extern "C" int surrogate_set_lr(ot_surrogate* s, float lr) {
 static void begin_step(ot_surrogate* s) {
   s->t += 1;
   s->step_adam = ot::AdamArgs{s->lr, s->beta1, s->beta2, s->eps, ot::bias_correction(s->beta1, s->t),
-                              ot::bias_correction(s->beta2, s->t), s->device_step ? s->t_done_dev : nullptr};
+                              ot::bias_correction(s->beta2, s->t), s->device_step ? s->t_now_dev : nullptr};
   const Layer& lo = s->layers[s->L - 1];
   // a single layer with a small input width takes the small-K gradient kernels, which store
   s->fused_step = s->fuse_out && !(s->L == 1 && lo.in <= ot::kMaxSmallK);
@@ -1599,8 +1605,9 @@ static ot::AdamRest make_rest(ot_surrogate* s, int64_t n_partials, int64_t rows,
   r.v = s->v;
   r.pb = s->pb;
   r.n4 = s->n_flat / 4;
+  // fused: bf16 leaves the output bias to this pass, fp32 nothing of the output layer
   r.hole = s->fused_step ? lo.w_off / 4 : 0;
-  r.hole_len = s->fused_step ? (lo.b_off - lo.w_off) / 4 : 0;
+  r.hole_len = !s->fused_step ? 0 : s->precision == OT_BF16 ? (lo.b_off - lo.w_off) / 4 : r.n4 - r.hole;
   r.partials = s->loss_partials;
   r.n_partials = n_partials;
   r.inv_count = 1.0 / ((double)rows * (double)s->widths[s->L]);
@@ -1623,7 +1630,7 @@ static int adam_step(ot_surrogate* s, hipStream_t st, const ot::AdamRest& r) {
 // dY = 2 (Y - U) / (B D) into dz[L], per-block loss partials.
 static int forward_mse_f32(ot_surrogate* s, const float* x, int64_t ldx, const float* u, int64_t ldu,
                            const int32_t* u_rows, int64_t u_rows_max, int64_t b, hipStream_t st,
-                           int64_t* n_partials) {
+                           int64_t* n_partials, long long* step_now = nullptr) {
   const int L = s->L;
   const int64_t D = s->widths[L];
   ot::PhaseTimer& tm = s->timer;
@@ -1649,6 +1656,7 @@ static int forward_mse_f32(ot_surrogate* s, const float* x, int64_t ldx, const f
   g.target_rows_max = u_rows_max;
   g.scale = (float)(2.0 / ((double)b * (double)D));
   g.loss_partials = s->loss_partials;
+  g.step_now = step_now;
   *n_partials = make_plan(g.M, g.N, g.K, false).blocks;
   if (*n_partials > s->n_partials_cap) return ot::set_error(OT_E_STATE, "loss partial buffer too small");
   return run_gemm<Lay::KMajor, Lay::KMajor, 1>(s, g, Epi::Mse, st, "output forward+MSE", false, OT_PH_FWD_OUTPUT);
@@ -1669,9 +1677,8 @@ static int check_batch(ot_surrogate* s, const float* x, int64_t ldx, const float
 // The train step.  u_rows (nullable): target row j is u + u_rows[j] * ldu
 // (indices clamped to [0, u_rows_max]); targets_read (nullable): recorded on
 // the stream once every target has been read.
-static int train_step_launches(ot_surrogate* s, const float* x, int64_t ldx, const float* u, int64_t ldu,
-                               const int32_t* u_rows, int64_t u_rows_max, int64_t b, void* stream, float* loss_dev,
-                               hipEvent_t targets_read) {
+static int train_step(ot_surrogate* s, const float* x, int64_t ldx, const float* u, int64_t ldu, const int32_t* u_rows,
+                      int64_t u_rows_max, int64_t b, void* stream, float* loss_dev, hipEvent_t targets_read) {
   const int L = s->L;
   int rc;
   const int64_t D = s->widths[L];
@@ -1687,9 +1694,11 @@ static int train_step_launches(ot_surrogate* s, const float* x, int64_t ldx, con
     tm.next_call();
     return rc;
   }
-  if ((rc = forward_mse_f32(s, x, ldx, u, ldu, u_rows, u_rows_max, b, st, &n_partials))) return rc;
+  if ((rc = forward_mse_f32(s, x, ldx, u, ldu, u_rows, u_rows_max, b, st, &n_partials,
+                            s->device_step ? s->t_now_dev : nullptr)))
+    return rc;
   if (targets_read) OT_HIP(hipEventRecord(targets_read, st));
-  const ot::AdamRest rest = make_rest(s, n_partials, b, loss_dev);
+  ot::AdamRest rest = make_rest(s, n_partials, b, loss_dev);
   bool rest_done = false;
 
   // weight and bias gradient of layer l: dW = dZ^T A_in, db = column sums of
@@ -1782,10 +1791,19 @@ static int train_step_launches(ot_surrogate* s, const float* x, int64_t ldx, con
                            nA);
         OT_LAUNCHED("hidden_bwd_small_kernel");
         const int64_t n_out = l2.out * l1.out + l2.out + l1.out * (l1.in + 1);
-        hipLaunchKernelGGL(ot::hidden_bwd_reduce_kernel, dim3((unsigned)ot::ceil_div(n_out, 256)), dim3(256), 0, st,
+        ot::HiddenAdam ha{s->grads, nullptr, s->m, s->v, l1.w_off, l1.b_off, l2.w_off, l2.b_off, s->step_adam};
+        ot::AdamRest loss{};
+        if (s->fused_step) {          // these layers and the loss are done here
+          ha.p = s->params;
+          loss = rest;
+          rest.hole = 0;
+          rest.hole_len = rest.n4;
+          rest.partials = nullptr;
+        }
+        hipLaunchKernelGGL(ot::hidden_bwd_reduce_kernel,
+                           dim3((unsigned)(ot::ceil_div(n_out, 256) + (loss.partials ? 1 : 0))), dim3(256), 0, st,
                            s->hs_part1, n_rt, s->hs_part2, s->hs_part2b, n_kc, (int)l1.in, (int)l1.out, (int)l2.out,
-                           s->grads + l1.w_off, l1.ldw, s->grads + l1.b_off, s->grads + l2.w_off, l2.ldw,
-                           s->grads + l2.b_off);
+                           l1.ldw, l2.ldw, ha, loss);
         OT_LAUNCHED("hidden_bwd_reduce_kernel");
         break;
       }
@@ -1802,21 +1820,8 @@ static int train_step_launches(ot_surrogate* s, const float* x, int64_t ldx, con
   }
   if (L >= 2) tm.mark(st, OT_PH_BWD_HIDDEN, 1);
   if (defer_out && (rc = wgrad(L))) return rc;
-  if (!rest_done) rc = adam_step(s, st, rest);
+  if (!rest_done && (rest.n4 > rest.hole_len || rest.partials)) rc = adam_step(s, st, rest);
   tm.next_call();
-  return rc;
-}
-
-// One train step; with the device step counter on, its last launch advances
-// the counter that the step's Adam kernels read.
-static int train_step(ot_surrogate* s, const float* x, int64_t ldx, const float* u, int64_t ldu,
-                      const int32_t* u_rows, int64_t u_rows_max, int64_t b, void* stream, float* loss_dev,
-                      hipEvent_t targets_read) {
-  int rc = train_step_launches(s, x, ldx, u, ldu, u_rows, u_rows_max, b, stream, loss_dev, targets_read);
-  if (rc == OT_OK && s->device_step) {
-    hipLaunchKernelGGL(ot::step_done_kernel, dim3(1), dim3(64), 0, static_cast<hipStream_t>(stream), s->t_done_dev);
-    OT_LAUNCHED("step_done_kernel");
-  }
   return rc;
 }
 
@@ -1826,13 +1831,13 @@ extern "C" int surrogate_set_device_step(ot_surrogate* s, int32_t enable) {
   OT_REQUIRE(enable == 0 || enable == 1, "surrogate_set_device_step: enable must be 0 or 1");
   if ((enable != 0) == s->device_step) return OT_OK;
   if (enable) {
-    if (!s->t_done_dev) {
-      int rc = salloc((void**)&s->t_done_dev, sizeof(long long));
+    if (!s->t_now_dev) {
+      int rc = salloc((void**)&s->t_now_dev, sizeof(long long));
       if (rc) return rc;
     }
     OT_HIP(hipDeviceSynchronize());
     const long long t = s->t;
-    OT_HIP(hipMemcpy(s->t_done_dev, &t, sizeof t, hipMemcpyHostToDevice));
+    OT_HIP(hipMemcpy(s->t_now_dev, &t, sizeof t, hipMemcpyHostToDevice));
     s->device_step = true;
     return OT_OK;
   }
@@ -1966,7 +1971,7 @@ extern "C" int surrogate_restore(ot_surrogate* s, const void* buf, int64_t bytes
   s->eps = hp[3];
   if (s->device_step) {
     const long long td = t;
-    OT_HIP(hipMemcpy(s->t_done_dev, &td, sizeof td, hipMemcpyHostToDevice));
+    OT_HIP(hipMemcpy(s->t_now_dev, &td, sizeof td, hipMemcpyHostToDevice));
   }
   return OT_OK;
 }

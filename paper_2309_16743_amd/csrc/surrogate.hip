@@ -1054,7 +1054,10 @@ constexpr Prod prod_of() {
 // Input gradients: over long k ranges the ping-pong kernel in splits until about two
 // blocks per CU, keeping at least 32 k tiles per split (200 x 1024, k 200000: 110
 // against 369 us on 128 x 128); else 256 x 128 tiles of the pipelined kernel with at
-// least 10 k tiles per split (512 x 512, k 19616: 23 against 38 us); 128 x 256 tiles
+// least 10 k tiles per split (512 x 512, k 19616: 23 against 38 us; k of 4096 and more
+// only, so that hidden layers' gradients keep whole sums: their operands are rounded to
+// bf16 again by the next layer, which turns another order into 1.9e-4 of the outputs of
+// a 2048-2048-2048 net after one step); 128 x 256 tiles
 // up to 128 rows (64 x 1024, k 300000: 125 against 178 us; 100 x 512, k 200000: 45 against 66).
 // Others with the 32-deep k tile kernels when k is a multiple of 32 and the tiles
 // give about one block per CU or more (forward products keep 32 k tiles per
@@ -1094,7 +1097,8 @@ Plan make_plan_b(int64_t M, int64_t N, int64_t K, bool allow_split, Prod prod, b
     const int64_t t = tiles_b(kBPipe, M, N);
     int64_t sp = 1;
     if (allow_split)
-      while (t * sp < 4 * kCUs - 64 && K / (2 * sp) >= (prod == Prod::InputGrad ? 10 : 32) * kPipeBK) sp *= 2;
+      while (t * sp < 4 * kCUs - 64 && K / (2 * sp) >= (prod == Prod::InputGrad && K >= 4096 ? 10 : 32) * kPipeBK)
+        sp *= 2;
     if (t * sp >= kCUs - 16) return plan(kBPipe, sp);
   }
   const int64_t t128 = tiles_b(kB128, M, N);

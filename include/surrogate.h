@@ -58,8 +58,10 @@ enum ot_surrogate_flags { OT_SURROGATE_KEEP_GRADS = 1 };
 
 /* Create an MLP with n_widths - 1 layers (2 <= n_widths <= 16, every width in
  * [1, 2^26]), parameters initialised from `seed` as above, Adam state zero.
- * max_batch: rows the train / predict workspaces are first sized for (grown
- * on demand).  flags: 0 or OT_SURROGATE_KEEP_GRADS.
+ * max_batch: rows of the largest train step that the workspaces are first sized
+ * for (a larger step replaces them).  They hold prediction passes of 256 rows at
+ * least, and the split-K partials of any step or pass of up to these rows, so
+ * that no smaller call allocates.  flags: 0 or OT_SURROGATE_KEEP_GRADS.
  * Errors: OT_E_INVAL, OT_E_NOMEM, OT_E_HIP. */
 int surrogate_create(ot_surrogate** out, const int64_t* widths, int32_t n_widths,
                      int32_t precision, float lr, float beta1, float beta2, float eps,
@@ -97,7 +99,10 @@ int surrogate_set_lr(ot_surrogate* s, float lr);
  * counter on, surrogate_get_adam_state and surrogate_checkpoint read the
  * device's count, surrogate_restore sets it, and enable = 0 copies it back to
  * the host.  A captured step also fixes the learning rate, the batch size,
- * the buffers and the stream it was captured with.  Errors: OT_E_INVAL,
+ * the buffers and the stream it was captured with.  Workspaces that a captured
+ * call (a train step, an evaluation or a prediction) may name are kept until
+ * surrogate_destroy also when a larger train step replaces them, so its graph
+ * may be replayed until then, whatever calls come between.  Errors: OT_E_INVAL,
  * OT_E_NOMEM, OT_E_HIP. */
 int surrogate_set_device_step(ot_surrogate* s, int32_t enable);
 

@@ -10,6 +10,7 @@
 #include <string>
 #include <vector>
 
+#include "intmath.h"
 #include "ot_status.h"
 
 namespace ot {
@@ -17,8 +18,6 @@ namespace ot {
 // Record a message for ot_last_error() on this thread and return `code`.
 int set_error(int code, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 void clear_error();
-
-inline int64_t round_up(int64_t v, int64_t m) { return (v + m - 1) / m * m; }
 
 // Per-phase HIP-event timing of the kernels one call enqueues (profiling
 // hook).  begin() creates start/end events for max_calls calls of every phase
@@ -57,7 +56,6 @@ struct PhaseTimer {
   int end(double* ms, int64_t* counts);
   void release();
 };
-inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Sequential writer / reader of a checkpoint blob in caller-owned host memory.
 // Every access is bounds-checked; ok() turns false at the first overrun and

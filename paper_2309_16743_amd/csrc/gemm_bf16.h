@@ -545,11 +545,6 @@ hipError_t launch_gemm_bf16(const GemmBArgs& g, int64_t splits, hipStream_t stre
   return hipGetLastError();
 }
 
-template <int FM, int FN>
-constexpr int64_t gemm_bf16_tiles(int64_t M, int64_t N) {
-  return ((M + 32 * FM - 1) / (32 * FM)) * ((N + 32 * FN - 1) / (32 * FN));
-}
-
 
 // ---------------------------------------------------------------------------
 // Pipelined bf16 GEMM for the large output-layer products.
@@ -840,11 +835,6 @@ hipError_t launch_gemm_bf16_pipe(const GemmBArgs& g, int64_t splits, hipStream_t
   hipExtLaunchKernelGGL((gemm_bf16_pipe_kernel<BM, BN, BK, S, OCC, LA, LB, EPI, NWN>),
                         dim3((unsigned)tiles, (unsigned)splits), dim3(128 * NWN), 0, stream, t0, t1, 0, g);
   return hipGetLastError();
-}
-
-template <int BM, int BN>
-constexpr int64_t gemm_bf16_pipe_tiles(int64_t M, int64_t N) {
-  return ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
 }
 
 // Ping-pong variant: 256 x 256 block tile, k tile 32, eight wavefronts in two

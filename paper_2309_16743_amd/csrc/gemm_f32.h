@@ -510,9 +510,4 @@ hipError_t launch_gemm_f32(const GemmArgs& g, int64_t splits, hipStream_t stream
   return hipGetLastError();
 }
 
-template <int WGM, int WGN, int FM, int FN>
-constexpr int64_t gemm_tiles(int64_t M, int64_t N) {
-  return ((M + 16 * FM * WGM - 1) / (16 * FM * WGM)) * ((N + 16 * FN * WGN - 1) / (16 * FN * WGN));
-}
-
 }  // namespace ot

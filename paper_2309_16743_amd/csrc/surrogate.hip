@@ -21,11 +21,11 @@
 #include "gemm_f32x3.h"
 #include "hidden_small.h"
 #include "philox.h"
+#include "plan.h"
 #include "surrogate.h"
 
 namespace ot {
 
-constexpr int kMaxSmallK = 16;   // layer 1 with in <= 16 uses the small-K kernels
 
 // ------------------------------------------------------------------ small kernels
 // Parameter initialisation: element e of layer `layer` (flat over W then b)
@@ -559,7 +559,6 @@ struct ot_surrogate {
   float* v = nullptr;
   float lr = 1e-3f, beta1 = 0.9f, beta2 = 0.999f, eps = 1e-8f;
   int64_t t = 0;
-  bool no_alloc = false;      // inside surrogate_predict_noalloc: workspaces must not grow
   bool fuse_out = false;      // output-layer Adam fused into its weight-gradient epilogue
   bool fused_step = false;    // ... and the current step took that path
   ot::AdamArgs step_adam{};   // Adam scalars of the current step
@@ -574,7 +573,7 @@ struct ot_surrogate {
   std::vector<float*> act;   // act[l] = A_l, l = 1..L-1 (index 0 unused)
   std::vector<float*> dz;    // dz[l] = dZ_l, l = 1..L (dz[L] = dY)
   std::vector<int64_t> ld;   // ld[l] = round_up(widths[l], 4)
-  float* splitws = nullptr;     // split-K partial products
+  float* splitws = nullptr;     // split-K partial products (split_need)
   int64_t splitws_elems = 0;
   float* rsws = nullptr;        // split-K partial row sums (bias gradients)
   int64_t rsws_elems = 0;
@@ -583,6 +582,10 @@ struct ot_surrogate {
   float* l1_part = nullptr;
   int64_t l1_part_elems = 0;
   bool small_hidden = false;    // fp32 6 -> H1 -> H2 -> D net with H1, H2 <= 256: fused narrow-layer kernels
+  // A call was captured: its graph holds workspace addresses, so workspaces that
+  // are replaced from then on are kept (retired) until the surrogate is destroyed.
+  bool captured = false;
+  std::vector<void*> retired;
   float* hs_part1 = nullptr;    // their partial sums (layer-1 gradient per row tile, layer-2 per k split)
   float* hs_part2 = nullptr;
   float* hs_part2b = nullptr;
@@ -594,7 +597,6 @@ struct ot_surrogate {
   std::vector<uint16_t*> act16;            // act16[l] = bf16(A_l), l = 1..L-1
   std::vector<uint16_t*> dz16;             // dz16[l] = bf16(dZ_l), l = 1..L (dz16[L] = dY)
   float* colsum = nullptr;                 // per m-tile column sums of dY (output bias gradient)
-  int64_t colsum_elems = 0;
 };
 
 namespace {
@@ -602,6 +604,12 @@ namespace {
 using ot::Epi;
 using ot::GemmArgs;
 using ot::Lay;
+using ot::NetShape;
+using ot::Plan;
+using ot::Prod;
+using ot::kBPipe, ot::kBPipeW, ot::kBPipeH, ot::kB128, ot::kBK, ot::kPipeBK;
+using ot::kC128x128, ot::kC64x128, ot::kX128, ot::kX64, ot::kX32W, ot::kX64W, ot::kX64x128;
+using ot::make_plan, ot::make_plan_b;
 
 int salloc(void** p, size_t bytes) {
   hipError_t e = hipMalloc(p, bytes ? bytes : 16);
@@ -613,36 +621,49 @@ int salloc(void** p, size_t bytes) {
   return OT_OK;
 }
 
+// Give a workspace back, or keep it for the graphs that may name it.
+template <class T>
+void drop(ot_surrogate* s, T*& p) {
+  if (p && s->captured) s->retired.push_back(p);
+  else (void)hipFree(p);
+  p = nullptr;
+}
+
 void free_workspace(ot_surrogate* s) {
-  for (float* p : s->act) (void)hipFree(p);
-  for (float* p : s->dz) (void)hipFree(p);
-  for (uint16_t* p : s->act16) (void)hipFree(p);
-  for (uint16_t* p : s->dz16) (void)hipFree(p);
-  s->act.assign(s->L + 1, nullptr);
-  s->dz.assign(s->L + 1, nullptr);
-  s->act16.assign(s->L + 1, nullptr);
-  s->dz16.assign(s->L + 1, nullptr);
-  (void)hipFree(s->splitws);
-  (void)hipFree(s->rsws);
-  (void)hipFree(s->loss_partials);
-  (void)hipFree(s->l1_part);
-  (void)hipFree(s->hs_part1);
-  (void)hipFree(s->hs_part2);
-  (void)hipFree(s->hs_part2b);
-  s->hs_part1 = s->hs_part2 = s->hs_part2b = nullptr;
-  s->splitws = nullptr;
-  s->splitws_elems = 0;
-  s->rsws = nullptr;
-  s->rsws_elems = 0;
-  s->loss_partials = nullptr;
-  s->l1_part = nullptr;
+  for (auto& p : s->act) drop(s, p);
+  for (auto& p : s->dz) drop(s, p);
+  for (auto& p : s->act16) drop(s, p);
+  for (auto& p : s->dz16) drop(s, p);
+  drop(s, s->splitws);
+  drop(s, s->rsws);
+  drop(s, s->colsum);
+  drop(s, s->loss_partials);
+  drop(s, s->l1_part);
+  drop(s, s->hs_part1);
+  drop(s, s->hs_part2);
+  drop(s, s->hs_part2b);
+  s->splitws_elems = s->rsws_elems = 0;
   s->ws_rows = s->act_rows = 0;
+}
+
+// Before a call enqueues work that names workspaces.  (A stream that cannot be
+// asked, the null stream while others are captured, is not being captured.)
+void note_capture(ot_surrogate* s, hipStream_t st) {
+  if (s->captured) return;
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &status) != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  s->captured = status != hipStreamCaptureStatusNone;
 }
 
 void free_surrogate(ot_surrogate* s) {
   if (!s) return;
   (void)hipDeviceSynchronize();
+  s->captured = false;
   free_workspace(s);
+  for (void* p : s->retired) (void)hipFree(p);
   s->timer.release();
   (void)hipFree(s->params);
   (void)hipFree(s->grads);
@@ -652,7 +673,6 @@ void free_surrogate(ot_surrogate* s) {
   (void)hipFree(s->eval_acc);
   (void)hipFree(s->t_now_dev);
   (void)hipFree(s->pb);
-  (void)hipFree(s->colsum);
   delete s;
 }
 
@@ -662,14 +682,13 @@ constexpr int64_t kL1Parts = 32;
 // after batches of 10, 1000000 x 256 fp32: 340 us instead of 4 x 250).
 constexpr int64_t kPredictRows = 256;
 
-int refuse_alloc(const char* what) {
-  return ot::set_error(OT_E_STATE, "%s would allocate inside surrogate_predict_noalloc", what);
+NetShape net_shape(const ot_surrogate* s) {
+  return {s->widths, s->precision == OT_BF16, s->small_hidden, s->fuse_out};
 }
 
 // creating: the caller synchronises the device before the workspace is used.
 int ensure_workspace(ot_surrogate* s, int64_t rows, bool creating = false) {
   if (rows <= s->ws_rows) return OT_OK;
-  if (s->no_alloc) return refuse_alloc("the batch workspace");
   if (!creating) OT_HIP(hipDeviceSynchronize());
   free_workspace(s);
   const int L = s->L;
@@ -707,6 +726,15 @@ int ensure_workspace(ot_surrogate* s, int64_t rows, bool creating = false) {
     OT_LAUNCHED("zero_pads_kernel");
     if (!creating) OT_HIP(hipStreamSynchronize(0));
   }
+  const ot::SplitNeed split = ot::split_need(net_shape(s), rows, act_rows);
+  if ((rc = salloc((void**)&s->splitws, (size_t)split.partials * sizeof(float)))) return rc;
+  if ((rc = salloc((void**)&s->rsws, (size_t)split.rowsums * sizeof(float)))) return rc;
+  s->splitws_elems = split.partials;
+  s->rsws_elems = split.rowsums;
+  // column sums of dY, at most one row for each 64 rows of the batch
+  if (s->precision == OT_BF16 &&
+      (rc = salloc((void**)&s->colsum, (size_t)(ot::ceil_div(rows, 64) * s->ld[L]) * sizeof(float))))
+    return rc;
   // one loss partial per block of the output GEMM (64 x 64 tiles bound the count)
   s->n_partials_cap = ot::ceil_div(rows, 64) * ot::ceil_div(s->widths[L], 64) + 64;
   if ((rc = salloc((void**)&s->loss_partials, (size_t)s->n_partials_cap * sizeof(double)))) return rc;
@@ -722,96 +750,6 @@ int ensure_workspace(ot_surrogate* s, int64_t rows, bool creating = false) {
   s->ws_rows = rows;
   s->act_rows = act_rows;
   return OT_OK;
-}
-
-// Tile shapes (4 wavefronts each): 128 x 128, 64 x 128, 64 x 64 on fp32 MFMAs;
-// 128 x 128, 64 x 128, 64 x 64, 32 x 256 and 64 x 256 on three bf16 terms
-// (gemm_f32x3.h).
-enum Cfg : int { kC128x128 = 0, kC64x128 = 1, kC64x64 = 2, kX128 = 3, kX64 = 4, kX32W = 5, kX64W = 6, kX64x128 = 7 };
-
-int64_t tiles_of(int cfg, int64_t M, int64_t N) {
-  switch (cfg) {
-    case kC128x128: return ot::gemm_tiles<2, 2, 4, 4>(M, N);
-    case kC64x128: return ot::gemm_tiles<2, 2, 2, 4>(M, N);
-    case kX128: return ot::ceil_div(M, 128) * ot::ceil_div(N, 128);
-    case kX64x128: return ot::ceil_div(M, 64) * ot::ceil_div(N, 128);
-    case kX32W: return ot::ceil_div(M, 32) * ot::ceil_div(N, 256);
-    case kX64W: return ot::ceil_div(M, 64) * ot::ceil_div(N, 256);
-    default: return ot::gemm_tiles<2, 2, 2, 2>(M, N);
-  }
-}
-
-struct Plan {
-  int cfg = kC64x64;
-  int64_t splits = 1;     // k ranges actually launched
-  int64_t k_chunk = 0;
-  int64_t blocks = 0;
-};
-
-// The plan on three bf16 terms, or false where the fp32 MFMA kernel is as good:
-// below 4e8 flops launch and fill time dominate (49 x 15766 x 242: forward 18
-// against 20 us, gradients even or slower), a weight gradient over fewer than 128 rows is bound by its
-// Adam epilogue (1000000 x 256 over 10 rows: 1146 us on fp32 MFMAs, 1168 here),
-// and fewer than 192 blocks leave CUs idle.  Forward products are never split
-// here (their partials would need scratch that surrogate_predict_noalloc's
-// callers did not have to fit); 64 x 128 tiles when they give two blocks per CU
-// (1024 x 10000 x 256: 54 us, 61 on 64 x 64 tiles), else 64 x 64 (331 x 6561 x 437:
-// 32 us, 35 on 64 x 128).  Backward products are split until about 512 blocks
-// (two 128 x 128 blocks share a CU; more would queue behind them: 10000 x 256
-// over 1024 rows in 3 splits 39 us, in 4 47 us).
-bool make_plan_x3(int64_t M, int64_t N, int64_t K, bool backward, Plan* p) {
-  constexpr int64_t kCUs = 256;
-  if (2.0 * M * N * K < 4e8) return false;
-  const int wide = M <= 32 ? kX32W : kX64W;
-  if (!backward) {
-    if (M <= 64 && tiles_of(wide, M, N) >= kCUs) p->cfg = wide;
-    else p->cfg = tiles_of(kX64x128, M, N) >= 2 * kCUs ? kX64x128 : kX64;
-    if (tiles_of(p->cfg, M, N) < kCUs - 64) return false;
-    p->splits = 1;
-  } else {
-    p->cfg = (M <= 64 && N > 128) ? wide : (M <= 64 || N <= 64) ? kX64 : kX128;
-    const int64_t t = tiles_of(p->cfg, M, N);
-    p->splits = std::max<int64_t>(1, std::min<int64_t>(2 * kCUs / t, K / 128));
-    if (t * p->splits < kCUs - 64 || K < 128) return false;
-  }
-  p->k_chunk = ot::round_up(ot::ceil_div(K, p->splits), 16);
-  p->splits = std::max<int64_t>(1, ot::ceil_div(K, p->k_chunk));
-  p->blocks = tiles_of(p->cfg, M, N) * p->splits;
-  return true;
-}
-
-// Tile and k-split choice (measured on MI355X at the surrogate's shapes).
-// Whole tiles per CU matter more than tile size: a launch whose block count
-// leaves some CUs a block more than others loses that fraction, so the plan
-// aims for about 4 blocks per CU (960+) with 64 x 128 tiles, splits long k
-// ranges (>= 4096) over 128 x 128 tiles, splits medium ones over 64 x 64
-// tiles (>= 256 deep per split), and splits short problems down to 32-deep
-// ranges until every CU has a block.  The MSE epilogue needs whole sums and
-// is never split.
-Plan make_plan(int64_t M, int64_t N, int64_t K, bool allow_split, bool backward = false) {
-  constexpr int64_t kCUs = 256;
-  Plan p;
-  if (make_plan_x3(M, N, K, backward, &p)) return p;
-  p = Plan{};
-  if (tiles_of(kC64x128, M, N) >= 960 || !allow_split) {
-    p.cfg = kC64x128;
-    if (tiles_of(kC64x128, M, N) < kCUs) p.cfg = kC64x64;
-    if (!allow_split && tiles_of(kC64x64, M, N) < kCUs) p.cfg = kC64x64;
-  } else if (K >= 4096) {
-    p.cfg = kC128x128;
-    const int64_t t = tiles_of(kC128x128, M, N);
-    while (t * p.splits < 2 * kCUs - 32 && K / (2 * p.splits) >= 256) p.splits *= 2;
-  } else {
-    p.cfg = kC64x64;
-    const int64_t t = tiles_of(kC64x64, M, N);
-    while (t * p.splits < 960 && K / (2 * p.splits) >= 256) p.splits *= 2;
-    if (t * p.splits < kCUs)
-      while (t * p.splits < kCUs && K / (2 * p.splits) >= 32) p.splits *= 2;
-  }
-  p.k_chunk = ot::round_up(ot::ceil_div(K, p.splits), 16);
-  p.splits = std::max<int64_t>(1, ot::ceil_div(K, p.k_chunk));
-  p.blocks = tiles_of(p.cfg, M, N) * p.splits;
-  return p;
 }
 
 // Epilogues that a product of these layouts meets: forward (KMajor, KMajor),
@@ -855,41 +793,12 @@ hipError_t launch_epi(Epi epi, int cfg, const GemmArgs& g, int64_t splits, hipSt
   }
 }
 
-int ensure_colsum(ot_surrogate* s, int64_t elems) {
-  if (elems <= s->colsum_elems) return OT_OK;
-  if (s->no_alloc) return refuse_alloc("the column-sum buffer");
-  OT_HIP(hipDeviceSynchronize());
-  (void)hipFree(s->colsum);
-  s->colsum = nullptr;
-  s->colsum_elems = 0;
-  int rc = salloc((void**)&s->colsum, (size_t)elems * sizeof(float));
-  if (rc) return rc;
-  s->colsum_elems = elems;
-  return OT_OK;
-}
-
-int ensure_split_ws(ot_surrogate* s, int64_t elems, int64_t rs_elems) {
-  if (s->no_alloc && (elems > s->splitws_elems || rs_elems > s->rsws_elems))
-    return refuse_alloc("the split-K partials");
-  if (elems > s->splitws_elems) {
-    OT_HIP(hipDeviceSynchronize());
-    (void)hipFree(s->splitws);
-    s->splitws = nullptr;
-    s->splitws_elems = 0;
-    int rc = salloc((void**)&s->splitws, (size_t)elems * sizeof(float));
-    if (rc) return rc;
-    s->splitws_elems = elems;
-  }
-  if (rs_elems > s->rsws_elems) {
-    OT_HIP(hipDeviceSynchronize());
-    (void)hipFree(s->rsws);
-    s->rsws = nullptr;
-    s->rsws_elems = 0;
-    int rc = salloc((void**)&s->rsws, (size_t)rs_elems * sizeof(float));
-    if (rc) return rc;
-    s->rsws_elems = rs_elems;
-  }
-  return OT_OK;
+// The split-K workspace was sized for every plan (split_need).
+int check_split_ws(const ot_surrogate* s, int64_t elems, int64_t rs_elems, const char* what) {
+  if (elems <= s->splitws_elems && rs_elems <= s->rsws_elems) return OT_OK;
+  return ot::set_error(OT_E_STATE, "%s: %lld + %lld floats of split-K partials, above the %lld + %lld of the workspace",
+                       what, (long long)elems, (long long)rs_elems, (long long)s->splitws_elems,
+                       (long long)s->rsws_elems);
 }
 
 // C = epi(A B) with the plan's tile shape; split-K runs write partial sums to
@@ -921,7 +830,7 @@ int run_gemm(ot_surrogate* s, GemmArgs g, Epi epi, hipStream_t st, const char* w
     return OT_OK;
   }
   const int64_t ldws = ot::round_up(g.N, 4);
-  int rc = ensure_split_ws(s, p.splits * g.M * ldws, g.rowsum ? p.splits * g.M : 0);
+  int rc = check_split_ws(s, p.splits * g.M * ldws, g.rowsum ? p.splits * g.M : 0, what);
   if (rc) return rc;
   GemmArgs h = g;
   h.C = s->splitws;
@@ -1018,105 +927,9 @@ using ot::EpiB;
 using ot::GemmBArgs;
 using ot::LayB;
 
-// bf16 tiles: for large products the pipelined 256 x 128 kernel (k tile 32,
-// direct-to-LDS loads, two blocks per CU), its 128 x 256 shape for up to 128
-// rows, or the ping-pong 256 x 256 kernel (eight wavefronts, one block per CU);
-// 128 x 128 (4 x 4 fragments per wave) and 64 x 64 (2 x 2) with a k tile of 32
-// otherwise.
-enum CfgB : int { kB128 = 0, kB64 = 1, kBPipe = 2, kBPipeW = 3, kBPipeH = 4 };
-constexpr int kBK = 32;
-constexpr int kPipeBK = 32;
-
-int64_t tiles_b(int cfg, int64_t M, int64_t N) {
-  if (cfg == kBPipe) return ot::gemm_bf16_pipe_tiles<256, 128>(M, N);
-  if (cfg == kBPipeW) return ot::gemm_bf16_pipe_tiles<256, 256>(M, N);
-  if (cfg == kBPipeH) return ot::gemm_bf16_pipe_tiles<128, 256>(M, N);
-  return cfg == kB128 ? ot::gemm_bf16_tiles<4, 4>(M, N) : ot::gemm_bf16_tiles<2, 2>(M, N);
-}
-
-// Rows of a tile.
-int64_t tile_rows_b(int cfg) {
-  return (cfg == kBPipe || cfg == kBPipeW) ? 256 : (cfg == kB128 || cfg == kBPipeH) ? 128 : 64;
-}
-
-enum class Prod : int { Forward, InputGrad, WeightGrad };
 template <LayB LA, LayB LB>
 constexpr Prod prod_of() {
   return LB == LayB::KMajor ? Prod::Forward : LA == LayB::KMajor ? Prod::InputGrad : Prod::WeightGrad;
-}
-
-// Wide forward products (about a tile per CU or more) are not split.  Up to 64
-// rows they stream the weights through 64 x 64 tiles (1 row, 1000000 x 1024: 355
-// us, 592 on 128 x 128), up to 128 through the pipelined kernel's 128 x 256 (100
-// rows: 508 against 638 us), above through the ping-pong kernel's 256 x 256 (200
-// rows, 1000000 x 2048: 1246 against 2115 us on 128 x 128, 1417 on 128 x 256);
-// rows past the operand are read from its last one.
-// Input gradients: over long k ranges the ping-pong kernel in splits until about two
-// blocks per CU, keeping at least 32 k tiles per split (200 x 1024, k 200000: 110
-// against 369 us on 128 x 128); else 256 x 128 tiles of the pipelined kernel with at
-// least 10 k tiles per split (512 x 512, k 19616: 23 against 38 us; k of 4096 and more
-// only, so that hidden layers' gradients keep whole sums: their operands are rounded to
-// bf16 again by the next layer, which turns another order into 1.9e-4 of the outputs of
-// a 2048-2048-2048 net after one step); 128 x 256 tiles
-// up to 128 rows (64 x 1024, k 300000: 125 against 178 us; 100 x 512, k 200000: 45 against 66).
-// Others with the 32-deep k tile kernels when k is a multiple of 32 and the tiles
-// give about one block per CU or more (forward products keep 32 k tiles per
-// split, so that their partials stay as small as they were), else 128 x 128 tiles
-// when they give about two blocks per CU; long k ranges are split over 128 x 128
-// tiles, shorter ones over 64 x 64.
-// pipe_ok: the 32-deep k tile kernels may be used (they have no row-sum output).
-Plan make_plan_b(int64_t M, int64_t N, int64_t K, bool allow_split, Prod prod, bool pipe_ok = true) {
-  constexpr int64_t kCUs = 256;
-  Plan p;
-  auto plan = [&](int cfg, int64_t sp) {
-    p.cfg = cfg;
-    p.k_chunk = ot::round_up(ot::ceil_div(K, sp), kPipeBK);
-    p.splits = std::max<int64_t>(1, ot::ceil_div(K, p.k_chunk));
-    p.blocks = tiles_b(cfg, M, N) * p.splits;
-    return p;
-  };
-  const bool deep = pipe_ok && K % kPipeBK == 0;
-  if (prod == Prod::Forward) {
-    if (M <= 64 && tiles_b(kB64, M, N) >= kCUs - 16) return plan(kB64, 1);
-    if (deep && N >= 256 && M > 64 && M <= 128 && tiles_b(kBPipeH, M, N) >= kCUs - 16) return plan(kBPipeH, 1);
-    if (deep && N >= 256 && M > 128 && tiles_b(kBPipeW, M, N) >= kCUs - 16) return plan(kBPipeW, 1);
-  }
-  if (deep && allow_split && M >= (prod == Prod::InputGrad ? 129 : 256) && N >= 256) {
-    const int64_t t = tiles_b(kBPipeW, M, N);
-    int64_t sp = 1;
-    while (t * sp < 2 * kCUs - 32 && K / (2 * sp) >= 32 * kPipeBK) sp *= 2;
-    if (sp > 1 && t * sp >= kCUs - 16) return plan(kBPipeW, sp);
-  }
-  if (deep && allow_split && prod == Prod::InputGrad && M <= 128 && N >= 128) {
-    const int64_t t = tiles_b(kBPipeH, M, N);
-    int64_t sp = 1;
-    while (t * sp < (M <= 32 ? 2 * kCUs - 32 : kCUs - 16) && K / (2 * sp) >= 10 * kPipeBK) sp *= 2;
-    if (t * sp >= kCUs - 16) return plan(kBPipeH, sp);
-  }
-  if (deep && M >= (prod == Prod::InputGrad ? 129 : 256) && N >= 128) {
-    const int64_t t = tiles_b(kBPipe, M, N);
-    int64_t sp = 1;
-    if (allow_split)
-      while (t * sp < 4 * kCUs - 64 && K / (2 * sp) >= (prod == Prod::InputGrad && K >= 4096 ? 10 : 32) * kPipeBK)
-        sp *= 2;
-    if (t * sp >= kCUs - 16) return plan(kBPipe, sp);
-  }
-  const int64_t t128 = tiles_b(kB128, M, N);
-  if (t128 >= 2 * kCUs - 32) {
-    p.cfg = kB128;
-  } else if (!allow_split) {
-    p.cfg = t128 >= kCUs - 16 ? kB128 : kB64;
-  } else {
-    p.cfg = K >= 4096 ? kB128 : kB64;
-    const int64_t t = tiles_b(p.cfg, M, N);
-    while (t * p.splits < 2 * kCUs - 32 && K / (2 * p.splits) >= 256) p.splits *= 2;
-    if (t * p.splits < kCUs)
-      while (t * p.splits < kCUs && K / (2 * p.splits) >= 64) p.splits *= 2;
-  }
-  p.k_chunk = ot::round_up(ot::ceil_div(K, p.splits), kBK);
-  p.splits = std::max<int64_t>(1, ot::ceil_div(K, p.k_chunk));
-  p.blocks = tiles_b(p.cfg, M, N) * p.splits;
-  return p;
 }
 
 template <LayB LA, LayB LB, EpiB E>
@@ -1160,7 +973,7 @@ int run_gemm_b(ot_surrogate* s, GemmBArgs g, hipStream_t st, const char* what, b
     return ot::set_error(OT_E_STATE, "%s: the MSE and Adam epilogues cannot be split", what);
   } else {
     const int64_t ldws = ot::round_up(g.N, 4);
-    int rc = ensure_split_ws(s, p.splits * g.M * ldws, g.rowsum ? p.splits * g.M : 0);
+    int rc = check_split_ws(s, p.splits * g.M * ldws, g.rowsum ? p.splits * g.M : 0, what);
     if (rc) return rc;
     GemmBArgs h = g;
     h.C = s->splitws;
@@ -1266,8 +1079,6 @@ int forward_mse_bf16(ot_surrogate* s, const float* x, int64_t ldx, const float* 
   g.step_now = bias_grad && s->device_step ? s->t_now_dev : nullptr;   // a train step, not an evaluation
   if (bias_grad) {
     // output bias gradient: per m-tile column sums of the rounded dY
-    const int64_t mtiles = ot::ceil_div(b, 64);
-    if ((rc = ensure_colsum(s, mtiles * s->ld[L]))) return rc;
     g.colsum = s->colsum;
     g.colsum_ld = s->ld[L];
   }
@@ -1278,7 +1089,7 @@ int forward_mse_bf16(ot_surrogate* s, const float* x, int64_t ldx, const float* 
                                                                 OT_PH_FWD_OUTPUT)))
     return rc;
   if (bias_grad) {
-    const int64_t used_mtiles = ot::ceil_div(b, tile_rows_b(pf.cfg));
+    const int64_t used_mtiles = ot::ceil_div(b, ot::tile_rows_b(pf.cfg));
     hipLaunchKernelGGL(ot::colsum_reduce_kernel, dim3((unsigned)ot::ceil_div(D, 256)), dim3(256), 0, st, s->colsum,
                        used_mtiles, D, s->ld[L], s->grads + lo.b_off);
     OT_LAUNCHED("colsum_reduce_kernel");
@@ -1686,8 +1497,9 @@ static int train_step(ot_surrogate* s, const float* x, int64_t ldx, const float*
   const int L = s->L;
   int rc;
   const int64_t D = s->widths[L];
-  if ((rc = ensure_workspace(s, b))) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  note_capture(s, st);
+  if ((rc = ensure_workspace(s, b))) return rc;
   begin_step(s);
 
   ot::PhaseTimer& tm = s->timer;
@@ -1883,6 +1695,7 @@ extern "C" int surrogate_eval_loss(ot_surrogate* s, const float* x, int64_t ldx,
   int rc = check_batch(s, x, ldx, u, ldu, "surrogate_eval_loss");
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  note_capture(s, st);
   const int64_t chunk = std::max<int64_t>(s->ws_rows, 1);
   const int64_t D = s->widths[s->L];
   for (int64_t r0 = 0; r0 < n; r0 += chunk) {
@@ -2040,6 +1853,7 @@ extern "C" int surrogate_predict(ot_surrogate* s, const float* x, int64_t ldx, i
   int rc = check_predict(s, x, ldx, y, ldy, "surrogate_predict");
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  note_capture(s, st);
   const int64_t chunk = std::max<int64_t>(s->act_rows, 1);
   for (int64_t r0 = 0; r0 < n; r0 += chunk) {
     const int64_t rows = std::min(chunk, n - r0);
@@ -2094,6 +1908,7 @@ struct NoAllocLayout {
 NoAllocLayout noalloc_layout(const ot_surrogate* s, int64_t rows) {
   const int L = s->L;
   const bool bf = s->precision == OT_BF16;
+  const NetShape net = net_shape(s);
   NoAllocLayout lay;
   int64_t off = 0;
   for (int l = 1; l < L; ++l) {
@@ -2103,9 +1918,7 @@ NoAllocLayout noalloc_layout(const ot_surrogate* s, int64_t rows) {
   int64_t split = 0;
   for (int l = 1; l <= L; ++l) {
     const Layer& ly = s->layers[l - 1];
-    // hidden layers without a GEMM: bf16 layer 1, the fp32 small-K layer 1
-    // and the fp32 narrow-hidden kernels
-    if (l < L && (bf ? l == 1 : (s->small_hidden || (l == 1 && ly.in <= ot::kMaxSmallK)))) continue;
+    if (!net.forward_product(l)) continue;
     const Plan p = bf ? make_plan_b(rows, ly.out, ly.in, true, Prod::Forward) : make_plan(rows, ly.out, ly.in, true);
     if (p.splits > 1) split = std::max(split, p.splits * rows * ot::round_up(ly.out, 4));
   }
@@ -2116,7 +1929,7 @@ NoAllocLayout noalloc_layout(const ot_surrogate* s, int64_t rows) {
 }
 
 // Points the surrogate's activation and split-K workspaces at the scratch for
-// one call and forbids growing them; restores both on destruction.
+// one call; restores both on destruction.
 struct ScratchWorkspace {
   ot_surrogate* s;
   float* act[16];
@@ -2140,7 +1953,6 @@ struct ScratchWorkspace {
     s->splitws_elems = lay.split_elems;
     s->rsws = nullptr;
     s->rsws_elems = 0;
-    s->no_alloc = true;
   }
   ~ScratchWorkspace() {
     for (int l = 1; l < s->L; ++l) {
@@ -2151,7 +1963,6 @@ struct ScratchWorkspace {
     s->splitws_elems = splitws_elems;
     s->rsws = rsws;
     s->rsws_elems = rsws_elems;
-    s->no_alloc = false;
   }
 };
 

@@ -42,7 +42,12 @@
 //
 // Operand values of 2^60 or more (infinities among them): the terms of a split
 // could overflow or form inf * 0 where the fp32 product does not, so a block that
-// meets one sums its tile again in fp32 on the vector units.
+// meets one sums its tile again in fp32 on the vector units.  So does one that meets
+// a NaN in an MNMajor operand: values are split in pairs, whose remainders take 0
+// times each other, and there the two belong to different outputs.  (In a KMajor
+// operand they belong to the same one, which is NaN either way.)  Such a block takes
+// the fp32 tiles through LDS (a train step of 6-256-256-10000 on 1024 rows with one
+// NaN target column: 310 us, 197 without; 491 with operands read from memory per k).
 #pragma once
 
 #include "gemm_f32.h"
@@ -57,10 +62,12 @@ typedef float x3_f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr float kX3Huge = 1152921504606846976.f;   // 2^60
 
-// Three bf16 terms of 8 fp32 values, packed two per word; big = max(big, |x|).
+// Three bf16 terms of 8 fp32 values, packed two per word; big = max(big, |x|),
+// which a NaN among x leaves as it was or (NAN_TOO) turns into NaN.
 // The remainders come from v_dot2_f32_bf16, x + (-1) * term + 0 * other term,
 // which reads a term in place (7 instructions a pair instead of 11 with the
 // terms widened first) and is exact, since every remainder is representable.
+template <bool NAN_TOO>
 __device__ __forceinline__ void x3_split8(const float (&x)[8], x3_u32x4 (&t)[3], float& big) {
   // (-1, 0) and (0, -1); in registers, since as an inline constant -1.0 would not be a bf16 pair
   uint32_t c0 = 0x0000bf80u, c1 = 0xbf800000u;
@@ -69,7 +76,10 @@ __device__ __forceinline__ void x3_split8(const float (&x)[8], x3_u32x4 (&t)[3],
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     float a = x[2 * q], b = x[2 * q + 1];
-    big = fmaxf(fmaxf(fabsf(a), fabsf(b)), big);
+    if constexpr (NAN_TOO)
+      big = __builtin_elementwise_maximum(__builtin_elementwise_maximum(fabsf(a), fabsf(b)), big);   // v_maximum3_f32
+    else
+      big = fmaxf(fmaxf(fabsf(a), fabsf(b)), big);
 #pragma unroll
     for (int p = 0; p < 3; ++p) {
       const x3_bf16x2 w = __builtin_convertvector(f32x2{a, b}, x3_bf16x2);
@@ -157,7 +167,7 @@ struct X3Operand {
       const float x[8] = {v[i][0][0], v[i][0][1], v[i][0][2], v[i][0][3],
                           v[i][1][0], v[i][1][1], v[i][1][2], v[i][1][3]};
       x3_u32x4 t[3];
-      x3_split8(x, t, big);
+      x3_split8<L == Lay::MNMajor>(x, t, big);
       int at;
       if constexpr (L == Lay::KMajor) {
         int r = ci / 2;
@@ -169,6 +179,22 @@ struct X3Operand {
       }
 #pragma unroll
       for (int p = 0; p < 3; ++p) *reinterpret_cast<x3_u32x4*>(lds + p * PLANE + at) = t[p];
+    }
+  }
+  // the values as they are, [16][T]
+  __device__ __forceinline__ void store_f32(float* lds) const {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      if (!mine(i)) continue;
+      const int ci = threadIdx.x + i * 256;
+      if constexpr (L == Lay::KMajor) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) lds[(8 * (ci % 2) + e) * T + ci / 2] = v[i][e / 4][e % 4];
+      } else {
+        float* p = lds + ci / (T / 8) * T + 8 * (ci % (T / 8));
+        *reinterpret_cast<f32x4*>(p) = v[i][0];
+        *reinterpret_cast<f32x4*>(p + 4) = v[i][1];
+      }
     }
   }
   // Operand of one MFMA: 32 LDS rows / columns from b0, this lane's 8 k values.
@@ -315,11 +341,12 @@ __global__ __launch_bounds__(256, x3_waves(WGN, FM, FN)) void gemm_f32x3_kernel(
   const int64_t mw = m0 + WM * wm + 4 * (lane / 32), nw = n0 + WN * wn + (IL ? FN : 1) * (lane % 32);
   auto row_of = [&](int f, int r) { return mw + 32 * f + 8 * (r / 4) + r % 4; };
   auto col_of = [&](int h) { return nw + (IL ? h : 32 * h); };
-  float big = 0.f;                                       // largest |value| this thread has split
+  float big_a = 0.f, big_kb = 0.f;                       // largest |value| this thread has split, or NaN
+  float& big_b = LA == LB ? big_a : big_kb;              // (the maximum of a KMajor operand would drop the NaN)
   auto store = [&](int buf) {
     add_rowsum();
-    oa.store(smem + buf * BUF, big);
-    ob.store(smem + buf * BUF + OA::BYTES, big);
+    oa.store(smem + buf * BUF, big_a);
+    ob.store(smem + buf * BUF + OA::BYTES, big_b);
   };
   int64_t t = 0;
   if (nk > 0) {
@@ -351,30 +378,40 @@ __global__ __launch_bounds__(256, x3_waves(WGN, FM, FN)) void gemm_f32x3_kernel(
 #pragma unroll
     for (int h = 0; h < FN; ++h) acc[f][h] += low[f][h];
 
-  if (big >= kX3Huge) s_huge = 1;
+  if (!(big_a < kX3Huge && big_b < kX3Huge)) s_huge = 1;
   x3_barrier();
   if (__builtin_amdgcn_readfirstlane(s_huge)) {            // the same for the whole block
 #pragma unroll
     for (int f = 0; f < FM; ++f)
 #pragma unroll
       for (int h = 0; h < FN; ++h) acc[f][h] = x3_f32x16{};
-    for (int64_t k = kbeg; k < kend; ++k) {
-      float bk[FN];
+    float* fa = reinterpret_cast<float*>(smem);           // [16][BM], then [16][BN]
+    float* fb = fa + 16 * BM;
+    static_assert(64 * (BM + BN) <= 2 * BUF, "fp32 tile");
+    for (int64_t q = 0; q < nk; ++q) {
+      load(q);
+      x3_barrier();                                       // the tile before has been read
+      oa.store_f32(fa);
+      ob.store_f32(fb);
+      x3_barrier();
+#pragma unroll 1
+      for (int k = 0; k < 16; ++k) {
+        float bk[FN];
 #pragma unroll
-      for (int h = 0; h < FN; ++h) {
-        const int64_t n = min(col_of(h), g.N - 1);
-        bk[h] = (LB == Lay::KMajor) ? g.B[n * g.ldb + k] : g.B[k * g.ldb + n];
+        for (int h = 0; h < FN; ++h) bk[h] = fb[k * BN + WN * wn + (IL ? FN * (lane % 32) + h : 32 * h + lane % 32)];
+#pragma unroll
+        for (int f = 0; f < FM; ++f)
+#pragma unroll
+          for (int g4 = 0; g4 < 4; ++g4) {
+            const f32x4 ak = *reinterpret_cast<const f32x4*>(fa + k * BM + WM * wm + 32 * f + 8 * g4 + 4 * (lane / 32));
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+              for (int h = 0; h < FN; ++h) acc[f][h][4 * g4 + e] = fmaf(ak[e], bk[h], acc[f][h][4 * g4 + e]);
+          }
       }
-#pragma unroll
-      for (int f = 0; f < FM; ++f)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int64_t m = min(row_of(f, r), g.M - 1);
-          const float ak = (LA == Lay::KMajor) ? g.A[m * g.lda + k] : g.A[k * g.lda + m];
-#pragma unroll
-          for (int h = 0; h < FN; ++h) acc[f][h][r] = fmaf(ak, bk[h], acc[f][h][r]);
-        }
     }
+    x3_barrier();
   }
   if constexpr (LA == Lay::MNMajor) {
     if (do_rowsum) {                                      // uniform over the block

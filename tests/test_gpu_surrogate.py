@@ -670,3 +670,45 @@ def test_predict_beyond_split_range(value):
     scale = np.maximum(np.abs(ref), np.abs(A).max() * np.minimum(np.abs(np.nan_to_num(W, posinf=0.0)).max(axis=1), 1e38))
     assert np.all(np.abs(got - ref)[fin] <= 64 * 2.0 ** -24 * scale[fin])
     s.close()
+
+
+@pytest.mark.parametrize("value", [2.0 ** 90, 3.3e38, np.inf, np.nan])
+@pytest.mark.parametrize("flags", ["keep_grads", "fused"])
+@pytest.mark.parametrize("widths,B", [((24, 9001), 1000),            # weight gradient in splits
+                                      ((6, 64, 160, 40000), 200)])   # unsplit; input gradient in splits
+def test_gradients_beyond_split_range(widths, B, flags, value):
+    """A target column far out of range makes one column of dY reach beyond the
+    range of the bf16 split (or infinity, NaN) in the gradient products: the
+    weight rows, moments and bias entries of every other output are those of
+    fp32 arithmetic, and so, while they are finite, are the output's own row and the
+    hidden layers' gradients."""
+    from paper_2309_16743_amd import OT_SURROGATE_KEEP_GRADS
+    L, n = len(widths) - 1, 1234
+    params, X, U = problem(widths, B, seed=12)
+    U[:, n] = value
+    keep = flags == "keep_grads"
+    s = make_gpu(widths, params, B, flags=OT_SURROGATE_KEEP_GRADS if keep else 0)
+    s.train_step(padded_from(X), padded_from(U), loss=torch.zeros(1, device=DEV))
+    torch.cuda.synchronize()
+    clean = U.copy()
+    clean[:, n] = 1.0
+    _, grads = mlp.loss_and_grads(params, X.astype(np.float64), clean.astype(np.float64))
+    new = mlp.Adam(lr=1e-3).step(params, grads)
+    others = np.arange(widths[-1]) != n
+    W, b = s.get_params(L - 1)
+    (mW, mb), _, _ = s.get_adam_state(L - 1)
+    assert close(mW[others], 0.1 * grads[-1][0][others], 1e-4) and close(mb[others], 0.1 * grads[-1][1][others], 1e-4)
+    assert rel(W[others], new[-1][0][others]) < 1e-4 and rel(b[others], new[-1][1][others]) < 1e-4
+    if keep:
+        gW, gb = s.get_grads(L - 1)
+        assert close(gW[others], grads[-1][0][others], 1e-4) and close(gb[others], grads[-1][1][others], 1e-4)
+    if np.isfinite(value):
+        # fp32 sums of the B rows: products of dY (about value / (B D)) stay finite
+        _, full = mlp.loss_and_grads(params, X.astype(np.float64), U.astype(np.float64))
+        assert close(mW[n], 0.1 * full[-1][0][n], 1e-4)
+        for l in range(L - 1):
+            gW, gb = s.get_grads(l)
+            assert close(gW, full[l][0], 1e-4) and close(gb, full[l][1], 1e-4), l
+    else:
+        assert not np.isfinite(mW[n]).any() and not np.isfinite(mb[n])
+    s.close()

@@ -262,7 +262,8 @@ struct AdamRest {
   const float* g;
   float* m;
   float* v;
-  uint16_t* pb;            // bf16 copy of the weights (nullable)
+  uint16_t* pb;            // bf16 copy of the weights: of the groups of 4 before pb_n4
+  int64_t pb_n4;
   int64_t n4, hole, hole_len;
   const double* partials;  // loss partials of the output forward (nullable: no loss)
   int64_t n_partials;
@@ -318,7 +319,7 @@ __device__ __forceinline__ void adam_groups(const AdamRest& r, const AdamArgs& a
       __builtin_nontemporal_store(pp[u], P + j);
       __builtin_nontemporal_store(mm[u], Mv + j);
       __builtin_nontemporal_store(vv[u], V + j);
-      if (PB)   // bf16 copy of the updated master weights
+      if (j < r.pb_n4)   // bf16 copy of the updated master weights
         __builtin_nontemporal_store(u16x4{f2bf(pp[u][0]), f2bf(pp[u][1]), f2bf(pp[u][2]), f2bf(pp[u][3])}, PB + j);
     }
   }
@@ -329,7 +330,7 @@ __device__ __forceinline__ void adam_groups(const AdamRest& r, const AdamArgs& a
     P[j] = pp;
     Mv[j] = mm;
     V[j] = vv;
-    if (PB) PB[j] = u16x4{f2bf(pp[0]), f2bf(pp[1]), f2bf(pp[2]), f2bf(pp[3])};
+    if (j < r.pb_n4) PB[j] = u16x4{f2bf(pp[0]), f2bf(pp[1]), f2bf(pp[2]), f2bf(pp[3])};
   }
 }
 
@@ -593,7 +594,7 @@ struct ot_surrogate {
   double* eval_acc = nullptr;   // running sum of squared residuals of surrogate_eval_loss
   ot::PhaseTimer timer;
   // OT_BF16 only
-  uint16_t* pb = nullptr;                  // bf16 copy of the flat parameters
+  uint16_t* pb = nullptr;                  // bf16 copy of the flat parameters up to W_L, then zeros
   std::vector<uint16_t*> act16;            // act16[l] = bf16(A_l), l = 1..L-1
   std::vector<uint16_t*> dz16;             // dz16[l] = bf16(dZ_l), l = 1..L (dz16[L] = dY)
   float* colsum = nullptr;                 // per m-tile column sums of dY (output bias gradient)
@@ -1202,6 +1203,12 @@ int predict_bf16(ot_surrogate* s, const float* xr, int64_t ldx, int64_t rows, fl
   return run_gemm_b<LayB::KMajor, LayB::KMajor, EpiB::BiasF32>(s, g, st, "bf16 output forward", true);
 }
 
+// Round the parameters up to W_L (and the zeros up to b_L) to their bf16 copy.
+void launch_to_bf16(ot_surrogate* s) {
+  const int64_t n = s->layers[s->L - 1].b_off;
+  hipLaunchKernelGGL(ot::to_bf16_kernel, dim3((unsigned)ot::ceil_div(n, 256)), dim3(256), 0, 0, s->params, s->pb, n);
+}
+
 int check_input(ot_surrogate* s, const float* X, int64_t ldx) {
   OT_REQUIRE(X != nullptr, "input x is NULL");
   OT_REQUIRE(ldx >= s->widths[0], "ldx < input width");
@@ -1290,18 +1297,19 @@ extern "C" int surrogate_create(ot_surrogate** out, const int64_t* widths, int32
                        1.0 / std::sqrt((double)ly.in));
   }
   if (precision == OT_BF16) {
-    // the output input gradient reads up to kPipeBK - 1 weight rows past W_L (times zeros of dY's
-    // padding): the bias copy, then this zeroed tail
-    const int64_t tail = kPipeBK * s->layers[s->L - 1].ldw;
-    if ((rc = salloc((void**)&s->pb, (size_t)(s->n_flat + tail) * sizeof(uint16_t)))) return fail(rc);
+    // the output input gradient reads up to kPipeBK - 1 weight rows past W_L, times zeros of dY's
+    // padding: zeros too (the copy ends with W_L, whatever values b_L has)
+    const Layer& lo = s->layers[s->L - 1];
+    const int64_t tail = kPipeBK * lo.ldw;
+    if ((rc = salloc((void**)&s->pb, (size_t)(lo.b_off + tail) * sizeof(uint16_t)))) return fail(rc);
     ot::PadList pads{};
-    pads.p[0] = s->pb + s->n_flat;
+    pads.p[0] = s->pb + lo.b_off;
     pads.ld[0] = tail;
     pads.rows[0] = 1;
     pads.bytes[0] = 2;
     pads.n = 1;
     hipLaunchKernelGGL(ot::zero_pads_kernel, dim3(64, 1), dim3(256), 0, 0, pads);
-    hipLaunchKernelGGL(ot::to_bf16_kernel, dim3(fb), dim3(256), 0, 0, s->params, s->pb, s->n_flat);
+    launch_to_bf16(s);
   }
   if (hipGetLastError() != hipSuccess) return fail(ot::set_error(OT_E_HIP, "initialisation launch failed"));
   if ((rc = ensure_workspace(s, max_batch, true))) return fail(rc);
@@ -1341,8 +1349,7 @@ extern "C" int surrogate_set_params(ot_surrogate* s, int32_t layer, const float*
                        ly.in * sizeof(float), ly.out, hipMemcpyHostToDevice));
   if (b_host) OT_HIP(hipMemcpy(s->params + ly.b_off, b_host, ly.out * sizeof(float), hipMemcpyHostToDevice));
   if (s->pb) {
-    hipLaunchKernelGGL(ot::to_bf16_kernel, dim3((unsigned)ot::ceil_div(s->n_flat, 256)), dim3(256), 0, 0, s->params,
-                       s->pb, s->n_flat);
+    launch_to_bf16(s);
     OT_LAUNCHED("to_bf16_kernel");
     OT_HIP(hipDeviceSynchronize());
   }
@@ -1419,6 +1426,7 @@ static ot::AdamRest make_rest(ot_surrogate* s, int64_t n_partials, int64_t rows,
   r.m = s->m;
   r.v = s->v;
   r.pb = s->pb;
+  r.pb_n4 = s->pb ? lo.b_off / 4 : 0;
   r.n4 = s->n_flat / 4;
   // fused: bf16 leaves the output bias to this pass, fp32 nothing of the output layer
   r.hole = s->fused_step ? lo.w_off / 4 : 0;
@@ -1776,8 +1784,7 @@ extern "C" int surrogate_restore(ot_surrogate* s, const void* buf, int64_t bytes
   OT_HIP(hipDeviceSynchronize());
   for (float* dst : {s->params, s->m, s->v}) OT_HIP(hipMemcpy(dst, rd.take(n_flat * 4), n_flat * 4, hipMemcpyHostToDevice));
   if (s->pb) {
-    hipLaunchKernelGGL(ot::to_bf16_kernel, dim3((unsigned)ot::ceil_div(n_flat, 256)), dim3(256), 0, 0, s->params, s->pb,
-                       n_flat);
+    launch_to_bf16(s);
     OT_LAUNCHED("to_bf16_kernel");
     OT_HIP(hipDeviceSynchronize());
   }

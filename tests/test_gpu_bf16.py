@@ -362,3 +362,25 @@ def test_fused_steps_predict_and_restart_bf16():
             assert np.array_equal(a, c), l
     f.close()
     g.close()
+
+
+@pytest.mark.parametrize("widths,B,i", [((6, 16, 16, 40), 1, 4), ((6, 64, 96, 61450), 100, 50)])
+def test_infinite_output_bias_stays_in_its_products(widths, B, i):
+    """dY's rows are padded with zeros to whole k tiles of the input gradient;
+    the weight rows that meet the padding are zero whatever the parameters that
+    follow W_L hold.  One infinite bias makes its column of dY infinite, and each
+    hidden unit's gradient infinite with the sign of the weight, not NaN."""
+    params, X, U = problem(widths, B, seed=9)
+    params[-1][1][i] = np.inf
+    s = make_gpu(widths, params, B)
+    s.train_step(padded_from(X), padded_from(U))
+    torch.cuda.synchronize()
+    _, gb = s.get_grads(len(widths) - 3)
+    A = X.astype(np.float64)
+    for W, b in params[:-1]:
+        A = np.maximum(A @ W.T + b, 0.0)
+    Wi = params[-1][0][i]
+    active = A.max(axis=0) > 1e-2 * A.max()          # units that bf16 rounding leaves active in some row
+    assert active.sum() >= 4 and active[i % widths[-2]]       # the unit whose weight column holds the bias copy
+    assert np.array_equal(gb[active], np.sign(Wi[active]) * np.inf), gb
+    s.close()

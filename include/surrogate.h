@@ -59,9 +59,10 @@ enum ot_surrogate_flags { OT_SURROGATE_KEEP_GRADS = 1 };
 /* Create an MLP with n_widths - 1 layers (2 <= n_widths <= 16, every width in
  * [1, 2^26]), parameters initialised from `seed` as above, Adam state zero.
  * max_batch: rows of the largest train step that the workspaces are first sized
- * for (a larger step replaces them).  They hold prediction passes of 256 rows at
- * least, and the split-K partials of any step or pass of up to these rows, so
- * that no smaller call allocates.  flags: 0 or OT_SURROGATE_KEEP_GRADS.
+ * for (a larger step replaces them).  They hold prediction passes of 256 rows (as
+ * far as 64 MB hold the hidden activations) or max_batch if that is more, and the
+ * split-K partials of any step or pass of up to these rows, so that no smaller
+ * call allocates.  flags: 0 or OT_SURROGATE_KEEP_GRADS.
  * Errors: OT_E_INVAL, OT_E_NOMEM, OT_E_HIP. */
 int surrogate_create(ot_surrogate** out, const int64_t* widths, int32_t n_widths,
                      int32_t precision, float lr, float beta1, float beta2, float eps,

@@ -678,10 +678,6 @@ void free_surrogate(ot_surrogate* s) {
 }
 
 constexpr int64_t kL1Parts = 32;
-// Hidden activations are sized for this many rows at least, so that a
-// prediction of more rows than the batch reads the output weights once (40 rows
-// after batches of 10, 1000000 x 256 fp32: 340 us instead of 4 x 250).
-constexpr int64_t kPredictRows = 256;
 
 NetShape net_shape(const ot_surrogate* s) {
   return {s->widths, s->precision == OT_BF16, s->small_hidden, s->fuse_out};
@@ -698,7 +694,7 @@ int ensure_workspace(ot_surrogate* s, int64_t rows, bool creating = false) {
   // which the weight gradient may read (into results it drops) and the bf16
   // input gradient sums over: the padding is zero
   ot::PadList pads{};
-  const int64_t act_rows = std::max(rows, kPredictRows);
+  const int64_t act_rows = ot::pass_rows(net_shape(s), rows);
   auto with_zero_pad = [&](auto** p, int l, int64_t n) -> int {
     int rc = salloc((void**)p, (size_t)n * s->ld[l] * sizeof(**p));
     if (rc || s->ld[l] == s->widths[l]) return rc;

@@ -56,7 +56,14 @@ static NetShape net(std::vector<int64_t> w, bool bf16, bool fuse = true) {
 }
 
 int main() {
-  const int64_t act = 256;
+  // prediction passes: 256 rows or the batch, fewer where wide hidden layers take over 64 MB
+  const int64_t act = pass_rows(net({6, 64, 64, 256}, false), 32);
+  if (act != 256 || pass_rows(net({6, 2048, 2048, 2048, 1000000}, true), 1024) != 1024 ||
+      pass_rows(net({6, 32768, 32760, 8}, false), 1) != 256 || pass_rows(net({6, 1000000, 1}, false), 1) != 16 ||
+      pass_rows(net({6, 1000000, 1}, true), 3) != 33 || pass_rows(net({6, 1 << 26, 1}, false), 1) != 1) {
+    std::printf("pass rows\n");
+    return 1;
+  }
   check(net({6, 64, 64, 256}, false), 32, act);
   check(net({6, 256, 256, 10000}, false), 1024, 1024);
   check(net({6, 300, 437, 6561}, false), 331, 331);
@@ -78,7 +85,8 @@ int main() {
     for (int l = 1 + (int)(rng() % 3); l > 0; --l) w.push_back(rng() % 3 ? pick(4, 5000) : 32 * pick(1, 128));
     w.push_back(rng() % 3 ? pick(1, 2000000) : 32 * pick(1, 40000));
     const int64_t rows = pick(1, 3000);
-    check(net(w, bf16, rng() % 2), rows, std::max(rows, act));
+    const NetShape shape = net(w, bf16, rng() % 2);
+    check(shape, rows, pass_rows(shape, rows));
   }
   std::printf("ok\n");
 }

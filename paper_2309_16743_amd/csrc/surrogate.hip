@@ -683,6 +683,8 @@ NetShape net_shape(const ot_surrogate* s) {
   return {s->widths, s->precision == OT_BF16, s->small_hidden, s->fuse_out};
 }
 
+// Workspaces for train steps of up to `rows` rows.  When one cannot be allocated
+// there are none until a later call asks again.
 // creating: the caller synchronises the device before the workspace is used.
 int ensure_workspace(ot_surrogate* s, int64_t rows, bool creating = false) {
   if (rows <= s->ws_rows) return OT_OK;
@@ -1700,7 +1702,8 @@ extern "C" int surrogate_eval_loss(ot_surrogate* s, const float* x, int64_t ldx,
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   note_capture(s, st);
-  const int64_t chunk = std::max<int64_t>(s->ws_rows, 1);
+  if ((rc = ensure_workspace(s, 1))) return rc;
+  const int64_t chunk = s->ws_rows;
   const int64_t D = s->widths[s->L];
   for (int64_t r0 = 0; r0 < n; r0 += chunk) {
     const int64_t rows = std::min(chunk, n - r0);
@@ -1857,7 +1860,8 @@ extern "C" int surrogate_predict(ot_surrogate* s, const float* x, int64_t ldx, i
   if (rc) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
   note_capture(s, st);
-  const int64_t chunk = std::max<int64_t>(s->act_rows, 1);
+  if ((rc = ensure_workspace(s, 1))) return rc;
+  const int64_t chunk = s->act_rows;
   for (int64_t r0 = 0; r0 < n; r0 += chunk) {
     const int64_t rows = std::min(chunk, n - r0);
     if ((rc = predict_rows(s, x + r0 * ldx, ldx, rows, y + r0 * ldy, ldy, st))) return rc;

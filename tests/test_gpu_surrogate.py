@@ -712,3 +712,29 @@ def test_gradients_beyond_split_range(widths, B, flags, value):
     else:
         assert not np.isfinite(mW[n]).any() and not np.isfinite(mb[n])
     s.close()
+
+
+def test_calls_after_a_step_too_large_for_memory():
+    """A train step whose workspaces do not fit the device is refused before
+    anything is enqueued; predictions, evaluations and smaller steps after it get
+    workspaces of their own again."""
+    from paper_2309_16743_amd import load
+    from paper_2309_16743_amd._abi import OT_E_NOMEM
+    widths, B = (6, 64, 64, 1_000_000), 8
+    params, X, U = problem(widths, B, seed=13)
+    s = make_gpu(widths, params, B)
+    x, u = padded_from(X), padded_from(U)
+    y = [padded_from(np.zeros((B, widths[-1]), np.float32)) for _ in range(2)]
+    losses = torch.zeros(2, device=DEV)
+    for i in range(2):
+        s.predict(x, y[i])
+        s.eval_loss(x, u, losses[i:i + 1])
+        torch.cuda.synchronize()
+        if i == 0:              # 2^20 rows of dY alone would be 4 TB; x and u are not read
+            assert load().surrogate_train_step(s.handle, x.data_ptr(), 8, u.data_ptr(), widths[-1], 1 << 20, None,
+                                               None) == OT_E_NOMEM
+    assert torch.equal(y[0], y[1]) and losses[0].item() == losses[1].item()
+    s.train_step(x, u)
+    torch.cuda.synchronize()
+    assert s.get_adam_state(0)[2] == 1
+    s.close()

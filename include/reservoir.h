@@ -200,16 +200,18 @@ enum ot_reservoir_phase {
   OT_PH_PUT_ASSIGN = 0,  /* put: slot assignment and eviction draws */
   OT_PH_PUT_COPY = 1,    /* put: row copies into the slabs */
   OT_PH_SELECT = 2,      /* sample: batch draws and seen-count update */
-  OT_PH_GATHER = 3,      /* sample: row copies into the batch buffers */
+  OT_PH_GATHER = 3,      /* sample: row copies into the batch buffers.  A draw of input rows
+                            alone (x_dim <= 16) copies them in its own kernel (SELECT); while
+                            this phase is timed they take a launch of their own, about 2 us */
   OT_RESERVOIR_PHASES = 4
 };
 
 /* Profiling hook: time the kernels of every phase in phase_mask for the next
- * max_calls put or sample calls with HIP events on the ordering stream.  The
- * single-kernel phases PUT_COPY and GATHER hand their events to the launch
- * (hipExtLaunchKernel), which stamps them with the kernel's own start and
- * end; the others record events before and after their kernels.  Allocates 2
- * events per phase and call. */
+ * max_calls put or sample calls with HIP events on the stream that the call's
+ * work runs on.  The single-kernel phases PUT_COPY and GATHER hand their
+ * events to the launch (hipExtLaunchKernel), which stamps them with the
+ * kernel's own start and end; the others record events before and after their
+ * kernels.  Allocates 2 events per phase and call. */
 int reservoir_timing_begin(ot_reservoir* r, uint32_t phase_mask, int64_t max_calls);
 
 /* Wait for the recorded events and return summed milliseconds and counts per

@@ -5,7 +5,11 @@
 //   a b ~ a0 b0 + (a0 b1 + a1 b0) + (a0 b2 + a1 b1 + a2 b0),
 // summed in fp32.  The dropped terms are below 2^-25 |a b|, less than the
 // rounding of one fp32 product, so the results are as exact as fp32 MFMAs
-// give.  v_mfma_f32_32x32x16_bf16 does 16 times the flops of
+// give, for operands above about 2^-109 (the third term of smaller ones falls
+// below the smallest bf16 numbers, so they keep fewer bits).  The split and the
+// choice of products are those of Henry, Tang and Heinecke (Leveraging the bfloat16
+// Artificial Intelligence Datatype for Higher-Precision Computations, ARITH 2019).
+// v_mfma_f32_32x32x16_bf16 does 16 times the flops of
 // v_mfma_f32_16x16x4_f32 per cycle, so six products still leave 2.7 times.
 //
 // Measured (us, this kernel / gemm_f32_kernel; relative error against 64 bits):
@@ -14,13 +18,13 @@
 //   10000 x 256, k 1024 in 3 splits      39 / 62     1.0e-7 / 4.1e-7
 //   10 x 256, k 1000000 in 512 splits   177 / 590    4.2e-7 / 1.5e-6
 //   10 x 1000000, k 256                 250 / 358    1.0e-7 / 2.9e-7
-//   1024 x 10000, k 256, MSE epilogue    63 / 66     8.6e-8 / 2.9e-7
+//   1024 x 10000, k 256, MSE epilogue    55 / 66     8.6e-8 / 2.9e-7
 // 822 us are 1.0 PFLOP/s of bf16 products; torch's bf16 GEMM reaches 1.15 on the
 // same card, at the 1.75 GHz that it holds under such a load.  The forward
 // with k = 256 is bound by its epilogue: the blocks start together, so the
 // targets' reads and the results' writes (82 MB) hardly overlap other blocks'
-// products (targets read ahead of the main loop: 66 us; wave priorities by
-// block: no change).
+// products (while this kernel still spilled registers, at 63 us: targets read
+// ahead of the main loop 66 us; wave priorities by block no change).
 //
 // Operand storage, GemmArgs, epilogues and tile order are those of
 // gemm_f32_kernel.  Block: 256 threads, WGM x WGN wavefronts of (32 FM) x
@@ -519,7 +523,7 @@ __global__ __launch_bounds__(256, x3_waves(WGN, FM, FN)) void gemm_f32x3_kernel(
 #pragma unroll
   for (int f = 0; f < FM; ++f) {
     // targets or masks of the fragment's 16 rows: all loads in flight together
-    // (8 at a time: 1024 x 10000 x 256 in 74 us instead of 63)
+    // (8 at a time: 1024 x 10000 x 256 in 74 us when 16 took 63)
     constexpr int RG = 16;
 #pragma unroll
     for (int r0 = 0; r0 < 16; r0 += RG) {

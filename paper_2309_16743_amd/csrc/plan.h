@@ -45,8 +45,8 @@ struct Plan {
 // and fewer than 192 blocks leave CUs idle.  Forward products are never split
 // here (their partials would need scratch that surrogate_predict_noalloc's
 // callers did not have to fit); 64 x 128 tiles when they give two blocks per CU
-// (1024 x 10000 x 256: 54 us, 61 on 64 x 64 tiles), else 64 x 64 (331 x 6561 x 437:
-// 32 us, 35 on 64 x 128).  Backward products are split until about 512 blocks
+// (1024 x 10000 x 256 with the MSE epilogue: 55 us, 67 on 64 x 64 tiles), else 64 x
+// 64 (331 x 6561 x 437, the same: 34 us, 35 on 64 x 128).  Backward products are split until about 512 blocks
 // (two 128 x 128 blocks share a CU; more would queue behind them: 10000 x 256
 // over 1024 rows in 3 splits 39 us, in 4 47 us).
 // any_size: without the rule on flops (for bounds over a range of sizes).
@@ -135,19 +135,21 @@ inline int64_t tile_rows_b(int cfg) {
 enum class Prod : int { Forward, InputGrad, WeightGrad };
 
 // Wide forward products (about a tile per CU or more) are not split.  Up to 64
-// rows they stream the weights through 64 x 64 tiles (1 row, 1000000 x 1024: 355
-// us, 592 on 128 x 128), up to 128 through the pipelined kernel's 128 x 256 (100
-// rows: 508 against 638 us), above through the ping-pong kernel's 256 x 256 (200
+// rows they stream the weights through 64 x 64 tiles (predictions of 1000000 x 1024:
+// 367 us at 1 row, 571 on 128 x 128; 537 and 618 at 64 rows, where 128 x 256 tiles
+// would take 494), up to 128 through the pipelined kernel's 128 x 256 (100 rows: 508
+// us, 655 on 128 x 128, 718 on 64 x 64), above through the ping-pong kernel's 256 x 256 (200
 // rows, 1000000 x 2048: 1246 against 2115 us on 128 x 128, 1417 on 128 x 256);
 // rows past the operand are read from its last one.
 // Input gradients: over long k ranges the ping-pong kernel in splits until about two
 // blocks per CU, keeping at least 32 k tiles per split (200 x 1024, k 200000: 110
 // against 369 us on 128 x 128); else 256 x 128 tiles of the pipelined kernel with at
-// least 10 k tiles per split (512 x 512, k 19616: 23 against 38 us; k of 4096 and more
-// only, so that hidden layers' gradients keep whole sums: their operands are rounded to
-// bf16 again by the next layer, which turns another order into 1.9e-4 of the outputs of
-// a 2048-2048-2048 net after one step); 128 x 256 tiles
-// up to 128 rows (64 x 1024, k 300000: 125 against 178 us; 100 x 512, k 200000: 45 against 66).
+// least 10 k tiles per split (512 x 512, k 19616: 23 against 38 us; from k of 4096 on,
+// which hidden layers rarely reach: below it ranges of 32 k tiles as before, since each
+// other order of a hidden gradient's sums moves a few values to the next bf16 value, which
+// the layers before it pass on, 1.9e-4 of the outputs of a 2048-2048-2048 net after one
+// step); 128 x 256 tiles up to 128 rows (64 x 1024, k 300000: 125 against 178 us; 100
+// x 512, k 200000: 45 against 66).
 // Others with the 32-deep k tile kernels when k is a multiple of 32 and the tiles
 // give about one block per CU or more (forward products keep 32 k tiles per
 // split, so that their partials stay as small as they were), else 128 x 128 tiles

@@ -621,7 +621,7 @@ __global__ void iota_kernel(int32_t* occ, int64_t n) {
   if (i < n) occ[i] = (int32_t)i;
 }
 
-// Gather rows of the drawn slots into the caller's batch buffers.
+// Gather field rows (and, x_out set, input rows) of the drawn slots into the caller's batch buffers.
 // grid = b rows x `segs` segments per row, flattened (row-major).
 __global__ __launch_bounds__(kCopyThreads) void gather_kernel(
     const int32_t* __restrict__ slots, const float* __restrict__ xslab, int64_t ldxs,
@@ -630,10 +630,8 @@ __global__ __launch_bounds__(kCopyThreads) void gather_kernel(
   const int64_t row = (int64_t)blockIdx.x / segs, seg = (int64_t)blockIdx.x % segs;
   const int64_t slot = slots[row];
   const int64_t seg0 = seg * kCopySeg;
-  if (u_out) {
-    const int64_t n = min(kCopySeg, u_dim - seg0);
-    copy_segment<true, false>(u_out + row * lduo + seg0, uslab + slot * ldus + seg0, n, vec_ok != 0);
-  }
+  const int64_t n = min(kCopySeg, u_dim - seg0);
+  copy_segment<true, false>(u_out + row * lduo + seg0, uslab + slot * ldus + seg0, n, vec_ok != 0);
   if (x_out && seg == 0)
     for (int64_t c = threadIdx.x; c < x_dim; c += kCopyThreads)
       x_out[row * ldxo + c] = xslab[slot * ldxs + c];
@@ -997,7 +995,8 @@ extern "C" int reservoir_sample_batch(ot_reservoir* r, int64_t b, void* stream, 
   if (ticket_out) *ticket_out = ticket;
   ot::PhaseTimer& tm = r->timer;
   tm.mark(st, OT_PH_SELECT, 0);
-  // short input rows alone are copied by the draw itself (unless the gather is being timed)
+  // short input rows alone are copied by the draw itself, unless the gather is being timed (it is then a launch
+  // of its own, as for longer rows)
   const bool with_x = !dc.take && x_out && !u_out && r->x_dim <= 16 && !tm.on(OT_PH_GATHER);
   if (!dc.take) {
     hipLaunchKernelGGL(ot::select_kernel, dim3((unsigned)ot::ceil_div(b, 256)), dim3(256), 0, st,
@@ -1022,7 +1021,7 @@ extern "C" int reservoir_sample_batch(ot_reservoir* r, int64_t b, void* stream, 
   } else if (u_out) {
     hipEvent_t t0, t1;
     tm.kernel_events(OT_PH_GATHER, &t0, &t1);
-    const int vec_ok = (u_out == nullptr) || (aligned16(u_out) && (lduo % 4 == 0));
+    const int vec_ok = aligned16(u_out) && (lduo % 4 == 0);
     const int64_t segs = ot::ceil_div(r->u_dim, ot::kCopySeg);
     hipExtLaunchKernelGGL(ot::gather_kernel, dim3((unsigned)(segs * drawn)), dim3(ot::kCopyThreads), 0, st,
                           t0, t1, 0, (const int32_t*)slots, (const float*)r->xslab, r->ldxs,

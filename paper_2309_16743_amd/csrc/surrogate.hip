@@ -70,8 +70,7 @@ __global__ __launch_bounds__(256) void zero_pads_kernel(PadList l) {
 }
 
 // First layer with a small input width K (the 6 inputs (X, t)):
-// A1[m][n] = max(sum_k X[m][k] W[n][k] + b[n], 0) (or without ReLU when the
-// net has a single layer).  One thread per output column and kSmallRows rows: the
+// A1[m][n] = max(sum_k X[m][k] W[n][k] + b[n], 0).  One thread per output column and kSmallRows rows: the
 // column's weights (rows of ldw = round_up(K, 8) values, zero past K) are read once
 // with 16-byte loads, x rows are the same for a whole wavefront, and a wavefront
 // writes 64 consecutive outputs of a row.  Latency-bound; with 4 columns of one row per
@@ -82,7 +81,7 @@ template <int KP>                       // round_up(K, 8): 8 or 16
 __global__ __launch_bounds__(256) void small_k_forward_kernel(const float* __restrict__ X, int64_t ldx,
                                                               const float* __restrict__ W,
                                                               const float* __restrict__ bias, float* __restrict__ out,
-                                                              int64_t ldo, int64_t M, int64_t N, int K, int relu,
+                                                              int64_t ldo, int64_t M, int64_t N, int K,
                                                               uint16_t* __restrict__ out16) {
   const int64_t col_blocks = (N + 255) / 256;
   const int64_t n = (int64_t)blockIdx.x % col_blocks * 256 + threadIdx.x;
@@ -104,7 +103,7 @@ __global__ __launch_bounds__(256) void small_k_forward_kernel(const float* __res
     for (int k = 0; k < KP; ++k)
       if (k < K) acc = fmaf(X[m * ldx + k], w[k], acc);
     acc += b;
-    const float y = relu ? (acc > 0.f ? acc : 0.f) : acc;
+    const float y = acc > 0.f ? acc : 0.f;
     if (out16) out16[m * ldo + n] = f2bf(y);   // bf16 activations feed the bf16 GEMMs
     else out[m * ldo + n] = y;
   }
@@ -114,9 +113,9 @@ inline void launch_small_k_forward(const float* X, int64_t ldx, const float* W, 
                                    int64_t ldo, int64_t M, int64_t N, int64_t K, uint16_t* out16, hipStream_t st) {
   const dim3 grid((unsigned)(ceil_div(N, 256) * ceil_div(M, kSmallRows)));
   if (K <= 8)
-    hipLaunchKernelGGL(small_k_forward_kernel<8>, grid, dim3(256), 0, st, X, ldx, W, bias, out, ldo, M, N, (int)K, 1, out16);
+    hipLaunchKernelGGL(small_k_forward_kernel<8>, grid, dim3(256), 0, st, X, ldx, W, bias, out, ldo, M, N, (int)K, out16);
   else
-    hipLaunchKernelGGL(small_k_forward_kernel<16>, grid, dim3(256), 0, st, X, ldx, W, bias, out, ldo, M, N, (int)K, 1, out16);
+    hipLaunchKernelGGL(small_k_forward_kernel<16>, grid, dim3(256), 0, st, X, ldx, W, bias, out, ldo, M, N, (int)K, out16);
 }
 
 // First-layer weight gradient, partial sums over a slice of rows:
@@ -609,7 +608,7 @@ using ot::NetShape;
 using ot::Plan;
 using ot::Prod;
 using ot::kBPipe, ot::kBPipeW, ot::kBPipeH, ot::kB128, ot::kBK, ot::kPipeBK;
-using ot::kC128x128, ot::kC64x128, ot::kX128, ot::kX64, ot::kX32W, ot::kX64W, ot::kX64x128;
+using ot::kC128x128, ot::kC64x128, ot::kC64x64, ot::kX128, ot::kX64, ot::kX32W, ot::kX64W, ot::kX64x128;
 using ot::make_plan, ot::make_plan_b;
 
 int salloc(void** p, size_t bytes) {
@@ -765,15 +764,24 @@ hipError_t launch_cfg(int cfg, const GemmArgs& g, int64_t splits, hipStream_t st
   if constexpr (!meets<LA, LB>(EPI)) {
     return hipErrorInvalidValue;
   } else {
+    // on three bf16 terms: the tiles that make_plan_x3 gives forward products, which
+    // it never splits, and backward ones
+    constexpr bool forward = LB == Lay::KMajor;
+    if constexpr (!forward || EPI != Epi::SplitK) {
+      if (cfg == kX64) return ot::launch_gemm_f32x3<2, 2, 1, 1, LA, LB, EPI, ROLE>(g, splits, st, t0, t1);
+      if (cfg == kX32W) return ot::launch_gemm_f32x3<1, 4, 1, 2, LA, LB, EPI, ROLE>(g, splits, st, t0, t1);
+      if (cfg == kX64W) return ot::launch_gemm_f32x3<1, 4, 2, 2, LA, LB, EPI, ROLE>(g, splits, st, t0, t1);
+      if constexpr (forward) {
+        if (cfg == kX64x128) return ot::launch_gemm_f32x3<2, 2, 1, 2, LA, LB, EPI, ROLE>(g, splits, st, t0, t1);
+      } else {
+        if (cfg == kX128) return ot::launch_gemm_f32x3<2, 2, 2, 2, LA, LB, EPI, ROLE>(g, splits, st, t0, t1);
+      }
+    }
     switch (cfg) {
       case kC128x128: return ot::launch_gemm_f32<2, 2, 4, 4, LA, LB, EPI, 16, ROLE>(g, splits, st, t0, t1);
       case kC64x128: return ot::launch_gemm_f32<2, 2, 2, 4, LA, LB, EPI, 16, ROLE>(g, splits, st, t0, t1);
-      case kX128: return ot::launch_gemm_f32x3<2, 2, 2, 2, LA, LB, EPI, ROLE>(g, splits, st, t0, t1);
-      case kX64x128: return ot::launch_gemm_f32x3<2, 2, 1, 2, LA, LB, EPI, ROLE>(g, splits, st, t0, t1);
-      case kX64: return ot::launch_gemm_f32x3<2, 2, 1, 1, LA, LB, EPI, ROLE>(g, splits, st, t0, t1);
-      case kX32W: return ot::launch_gemm_f32x3<1, 4, 1, 2, LA, LB, EPI, ROLE>(g, splits, st, t0, t1);
-      case kX64W: return ot::launch_gemm_f32x3<1, 4, 2, 2, LA, LB, EPI, ROLE>(g, splits, st, t0, t1);
-      default: return ot::launch_gemm_f32<2, 2, 2, 2, LA, LB, EPI, 16, ROLE>(g, splits, st, t0, t1);
+      case kC64x64: return ot::launch_gemm_f32<2, 2, 2, 2, LA, LB, EPI, 16, ROLE>(g, splits, st, t0, t1);
+      default: return hipErrorInvalidValue;
     }
   }
 }

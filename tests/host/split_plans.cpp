@@ -18,6 +18,13 @@ static SplitNeed need_of(const NetShape& net, int64_t m, bool train) {
       std::printf("bad plan of %lld x %lld x %lld\n", (long long)M, (long long)N, (long long)K);
       std::exit(1);
     }
+    // the launches have three-term tiles for these only: forward ones are never split
+    const bool forward = prod == Prod::Forward;
+    if (!net.bf16 && ((forward && (p.cfg == kX128 || (p.cfg > kC64x64 && p.splits > 1))) ||
+                      (!forward && p.cfg == kX64x128))) {
+      std::printf("tiles %d of %lld x %lld x %lld\n", p.cfg, (long long)M, (long long)N, (long long)K);
+      std::exit(1);
+    }
     n.add(p.splits, M, N, rowsum);
   });
   return n;

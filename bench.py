@@ -67,6 +67,9 @@ if ROOT not in sys.path:
 
 PEAK_FP32_MFMA = 157.3e12      # MI355X dense fp32 matrix peak, FLOP/s
 PEAK_BF16_MFMA = 2.5e15        # MI355X dense bf16 matrix peak, FLOP/s
+# fp32 products of 4e8 flops and more run on the bf16 matrix cores as six products
+# of bf16 terms each (csrc/gemm_f32x3.h; smaller ones on fp32 MFMAs)
+X3_FLOPS, X3_PRODUCTS = 4e8, 6
 PEAK_HBM = 8.0e12              # MI355X HBM3E, bytes/s
 METRIC = "surrogate train samples/s at 1 MI355X; MFMA util of output layer; reservoir GB/s"
 
@@ -152,11 +155,11 @@ def stream_mode(args, w) -> str:
 
 def kernel_sources(label: str):
     csrc = os.path.join(ROOT, "paper_2309_16743_amd", "csrc")
-    files = ["common.h"]
+    files = ["common.h", "intmath.h"]
     if label.startswith("gemm_fp32"):
-        files += ["adam.h", "gemm_f32.h", "surrogate.hip"]
+        files += ["adam.h", "gemm_f32.h", "gemm_f32x3.h", "plan.h", "surrogate.hip"]
     elif label.startswith("gemm_bf16"):
-        files += ["adam.h", "gemm_bf16.h", "surrogate.hip"]
+        files += ["adam.h", "gemm_bf16.h", "plan.h", "surrogate.hip"]
     elif label == "adam_kernel":
         files += ["adam.h", "surrogate.hip"]
     else:
@@ -183,7 +186,8 @@ def kernel_matches(label: str, name: str) -> bool:
     if label.startswith("gemm_fp32"):
         lay = {"fwd_output": "(ot::Lay)0, (ot::Lay)0", "wgrad_output": "(ot::Lay)1, (ot::Lay)1",
                "igrad_output": "(ot::Lay)0, (ot::Lay)1"}[phase]
-        return "gemm_f32_kernel<" in name and lay in name and name.split(">(")[0].endswith(", 1")
+        return (("gemm_f32_kernel<" in name or "gemm_f32x3_kernel<" in name) and lay in name
+                and name.split(">(")[0].endswith(", 1"))
     lay = {"fwd_output": "(ot::LayB)0, (ot::LayB)0", "wgrad_output": "(ot::LayB)1, (ot::LayB)1",
            "igrad_output": "(ot::LayB)0, (ot::LayB)1"}[phase]
     return ("gemm_bf16_pipe_kernel<" in name or "gemm_bf16_pp_kernel<" in name) and lay in name
@@ -257,6 +261,23 @@ def gemm_flops(w) -> float:
     return 2.0 * w.batch * w.widths[-2] * w.widths[-1]
 
 
+def mfma_products(w) -> int:
+    """Matrix products behind one output-layer product."""
+    return X3_PRODUCTS if w.precision == "fp32" and gemm_flops(w) >= X3_FLOPS else 1
+
+
+def peak_mfma(w) -> float:
+    """Datasheet peak, in flops of the product, of the matrix unit that the output-layer GEMMs run on."""
+    n = mfma_products(w)
+    return PEAK_FP32_MFMA if w.precision == "fp32" and n == 1 else PEAK_BF16_MFMA / n
+
+
+def mfma_unit(w) -> str:
+    if mfma_products(w) > 1:
+        return "bf16 MFMA, six products of bf16 terms per fp32 product"
+    return f"{w.precision} MFMA"
+
+
 def out_weights(w) -> int:
     """Weights of the output layer (H x D), whose Adam update is fused into the
     weight-gradient GEMM (bf16) or its split-K reduction (fp32)."""
@@ -296,14 +317,13 @@ def put_bytes(w) -> float:
 
 def kernel_table(w, phases_ms: dict, res_ms: dict) -> dict:
     """Average duration and algorithmic rate of each timed phase."""
-    peak_mfma = PEAK_BF16_MFMA if w.precision == "bf16" else PEAK_FP32_MFMA
     out = {}
     for name, (ms, n) in phases_ms.items():
         avg = ms / max(n, 1)
         row = {"avg_us": round(avg * 1e3, 2), "launches": n}
         if name in ("fwd_output", "wgrad_output", "igrad_output"):
             rate = gemm_flops(w) / (avg * 1e-3)
-            row.update(achieved_tflops=round(rate / 1e12, 2), frac_mfma=round(rate / peak_mfma, 4))
+            row.update(achieved_tflops=round(rate / 1e12, 2), frac_mfma=round(rate / peak_mfma(w), 4))
         if (name == "wgrad_output" and w.precision == "bf16") or (name == "wgrad_reduce" and w.precision == "fp32"):
             rate = fused_adam_bytes(w) / (avg * 1e-3)     # the phase that applies the fused Adam update
             row.update(fused_adam=True, achieved_gbs=round(rate / 1e9, 1), frac_hbm=round(rate / PEAK_HBM, 4))
@@ -336,11 +356,11 @@ def roofline_entry(w, phase: str, avg_s: float) -> dict:
                 "per_launch_bytes": work, "per_launch_flops": gemm_flops(w),
                 "mfma_frac": round(gemm_flops(w) / avg_s / PEAK_BF16_MFMA, 4), "avg_us": round(avg_s * 1e6, 2)}
     if phase in ("fwd_output", "wgrad_output", "igrad_output"):
-        peak = PEAK_BF16_MFMA if w.precision == "bf16" else PEAK_FP32_MFMA
+        peak = peak_mfma(w)
         work = gemm_flops(w)
         label = f"gemm_{w.precision} ({phase})"
-        return {"bound": "mfma", "kernel": label,
-                "achieved": round(work / avg_s / 1e12, 2), "peak": peak / 1e12, "unit": "TFLOP/s",
+        return {"bound": "mfma", "kernel": label, "matrix_unit": mfma_unit(w),
+                "achieved": round(work / avg_s / 1e12, 2), "peak": round(peak / 1e12, 1), "unit": "TFLOP/s",
                 "frac": round(work / avg_s / peak, 4), "traffic": traffic_for(w.name, label),
                 "per_launch_flops": work, "avg_us": round(avg_s * 1e6, 2)}
     work = {"adam": adam_bytes(w), "gather": gather_bytes(w)}[phase]
@@ -351,10 +371,11 @@ def roofline_entry(w, phase: str, avg_s: float) -> dict:
             "per_launch_bytes": work, "avg_us": round(avg_s * 1e6, 2)}
 
 
-def achievable_rates(precision: str) -> dict:
+def achievable_rates(precision: str, products: int = 1) -> dict:
     """Rates this GPU reaches outside the library, measured live for context:
     a device-to-device copy of 1 GiB (read + write) and torch's GEMM on
-    8192 x 8192 x 8192 in the workload's precision."""
+    8192 x 8192 x 8192 in the workload's precision, or, where each of its
+    products takes several in bf16, the bf16 GEMM's rate over their number."""
     import torch
     dev = torch.device("cuda:0")
 
@@ -374,14 +395,16 @@ def achievable_rates(precision: str) -> dict:
     a.fill_(1.0)
     copy_gbs = 2 * CAL_FLOATS * 4 / (avg_ms(lambda: b.copy_(a), 5) * 1e-3) / 1e9
     del a, b
-    dt = torch.float32 if precision == "fp32" else torch.bfloat16
+    in_fp32 = precision == "fp32" and products == 1
     torch.backends.cuda.matmul.allow_tf32 = False
-    x = torch.ones(8192, 8192, device=dev, dtype=dt)
-    ms = avg_ms(lambda: torch.matmul(x, x), 3 if precision == "fp32" else 10)
+    x = torch.ones(8192, 8192, device=dev, dtype=torch.float32 if in_fp32 else torch.bfloat16)
+    ms = avg_ms(lambda: torch.matmul(x, x), 3 if in_fp32 else 10)
     del x
     torch.cuda.empty_cache()
-    return {"hbm_copy_gbs": round(copy_gbs, 1), "gemm_tflops": round(2 * 8192 ** 3 / (ms * 1e-3) / 1e12, 1),
-            "gemm": f"torch.matmul 8192^3 {'fp32' if precision == 'fp32' else 'bf16'}"}
+    return {"hbm_copy_gbs": round(copy_gbs, 1),
+            "gemm_tflops": round(2 * 8192 ** 3 / (ms * 1e-3) / products / 1e12, 1),
+            "gemm": "torch.matmul 8192^3 " + ("fp32" if in_fp32 else "bf16") +
+                    (f", over the {products} products of bf16 terms per product" if products > 1 else "")}
 
 
 def with_achievable(roof: dict, ach: dict) -> dict:
@@ -592,7 +615,7 @@ def timed_region(tr, w, K, profile_steps, stream, wrap_put):
     phase_avg_s = {p: sur_t[p][0] / sur_t[p][1] * 1e-3 for p in sur_phases if p in sur_t}
     put_avg_s = res_t["put_copy"][0] / res_t["put_copy"][1] * 1e-3 if "put_copy" in res_t else None
     dom_avg_s = g_ms / g_n * 1e-3 if dom_phase == "gather" else phase_avg_s[dom_phase]
-    achievable = achievable_rates(w.precision)      # after the timed region, which it does not disturb
+    achievable = achievable_rates(w.precision, mfma_products(w))      # after the timed region, which it does not disturb
     return dict(gpu_ms=gpu_ms, wall=wall, windows=windows, breakdown=breakdown, dom_phase=dom_phase,
                 achievable=achievable, dom_avg_s=dom_avg_s, gather_avg_s=g_ms / g_n * 1e-3,
                 phase_avg_s=phase_avg_s, put_avg_s=put_avg_s, loss=float(tr.loss.item()))
@@ -619,10 +642,10 @@ def steps_rate(tr, w, K, stream, wrap_put) -> dict:
 def output_layer_entry(w, phase_avg_s: dict) -> dict:
     """Rates of the output layer's three GEMMs (the dominant one measured in
     the timed region, the others on the eager steps that follow it):
-    forward (+ fused MSE) and input gradient against the MFMA peak of their
-    precision; the weight gradient too, and in bf16, where it applies Adam to
+    forward (+ fused MSE) and input gradient against the peak of the matrix
+    unit they run on; the weight gradient too, and in bf16, where it applies Adam to
     the output weights in its epilogue, also against HBM."""
-    peak = PEAK_BF16_MFMA if w.precision == "bf16" else PEAK_FP32_MFMA
+    peak = peak_mfma(w)
     out = {}
     for p in ("fwd_output", "igrad_output", "wgrad_output"):
         if p not in phase_avg_s:
@@ -634,7 +657,8 @@ def output_layer_entry(w, phase_avg_s: dict) -> dict:
             e.update(fused_adam=True, achieved_gbs=round(fused_adam_bytes(w) / t / 1e9, 1),
                      frac_hbm=round(fused_adam_bytes(w) / t / PEAK_HBM, 4))
         out[p] = e
-    out["peak_tflops"] = peak / 1e12
+    out["peak_tflops"] = round(peak / 1e12, 1)
+    out["matrix_unit"] = mfma_unit(w)
     return out
 
 
@@ -645,7 +669,8 @@ def reservoir_entry(w, r) -> dict:
     g_rate = gather_bytes(w) / r["gather_avg_s"]
     out = {"gather": {"achieved": round(g_rate / 1e9, 1), "unit": "GB/s", "frac_hbm": round(g_rate / PEAK_HBM, 4),
                       "avg_us": round(r["gather_avg_s"] * 1e6, 2), "bytes_per_launch": gather_bytes(w),
-                      "rows": "input rows only (the targets are read in place by the forward)"
+                      "rows": "input rows only (the targets are read in place by the forward); a launch of its own "
+                              "while it is timed, otherwise copied by the draw's kernel"
                       if not GATHERED_TARGETS else "input and field rows"}}
     if r.get("put_avg_s"):
         p_rate = put_bytes(w) / r["put_avg_s"]

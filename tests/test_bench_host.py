@@ -87,6 +87,28 @@ def test_roofline_labels_match_their_kernels(bench):
     assert not bench.kernel_matches("gather_kernel", "ot::gather_x_kernel(int const*, float const*, long)")
 
 
+def test_fp32_products_on_bf16_terms(bench):
+    """The fp32 labels match the three-term kernel too, its source files enter their
+    hash, and the fp32 workload that runs on it is held against the unit it uses."""
+    fwd = "void ot::gemm_f32x3_kernel<2, 2, 1, 2, (ot::Lay)0, (ot::Lay)0, (ot::Epi)3, 1>(ot::GemmArgs)"
+    igrad = "void ot::gemm_f32x3_kernel<2, 2, 2, 2, (ot::Lay)0, (ot::Lay)1, (ot::Epi)4, 1>(ot::GemmArgs)"
+    hidden = "void ot::gemm_f32x3_kernel<2, 2, 2, 2, (ot::Lay)0, (ot::Lay)1, (ot::Epi)4, 0>(ot::GemmArgs)"
+    assert bench.kernel_matches("gemm_fp32 (fwd_output)", fwd)
+    assert bench.kernel_matches("gemm_fp32 (igrad_output)", igrad)
+    assert not bench.kernel_matches("gemm_fp32 (fwd_output)", igrad)
+    assert not bench.kernel_matches("gemm_fp32 (igrad_output)", hidden)
+    names = {os.path.basename(f) for f in bench.kernel_sources("gemm_fp32 (fwd_output)")}
+    assert {"gemm_f32.h", "gemm_f32x3.h", "plan.h", "surrogate.hip"} <= names
+    assert all(os.path.exists(f) for label in ("gemm_fp32 (fwd_output)", "gemm_bf16 (fwd_output)", "adam_kernel",
+                                               "gather_kernel") for f in bench.kernel_sources(label))
+    heat, tiny, deep = (configs.ALL[n] for n in ("heat-100x100", "tiny-16x16", "deep-sine-1000x1000"))
+    assert bench.peak_mfma(heat) == 2.5e15 / 6 and bench.mfma_products(heat) == 6
+    assert bench.peak_mfma(tiny) == 157.3e12 and bench.mfma_unit(tiny) == "fp32 MFMA"
+    assert bench.peak_mfma(deep) == 2.5e15 and bench.mfma_products(deep) == 1
+    r = bench.roofline_entry(heat, "fwd_output", 55e-6)
+    assert abs(r["frac"] - 2 * 1024 * 256 * 10_000 / 55e-6 / (2.5e15 / 6)) < 1e-4
+
+
 def test_one_stream_for_latency_bound_workloads(bench):
     args = types.SimpleNamespace(one_stream=False)
     assert bench.one_stream(args, configs.ALL["tiny-16x16"])           # 32 x 256 x 4 B of targets

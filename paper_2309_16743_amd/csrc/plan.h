@@ -296,14 +296,12 @@ inline SplitNeed split_need(const NetShape& net, int64_t rows, int64_t act_rows)
       need.add(make_plan_f32(M, N, K, true).asked, M, N, rowsum);
     });
   };
-  auto groups_to = [&](int64_t top) {
-    for (int64_t m = 32; m < top + 32; m += 32) {
-      if (std::min(m, top) > 1) at(std::min(m, top) - 1);
-      at(std::min(m, top));
-    }
-  };
-  groups_to(rows);
-  groups_to(act_rows);
+  for (int64_t m = 32; m < act_rows + 32; m += 32) {
+    if (std::min(m, act_rows) > 1) at(std::min(m, act_rows) - 1);
+    at(std::min(m, act_rows));
+  }
+  if (rows > 1) at(rows - 1);
+  at(rows);
   return need;
 }
 

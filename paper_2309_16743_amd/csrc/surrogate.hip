@@ -572,7 +572,7 @@ struct ot_surrogate {
   int64_t act_rows = 0;      // rows of the hidden activations (>= ws_rows): what one prediction pass takes
   std::vector<float*> act;   // act[l] = A_l, l = 1..L-1 (index 0 unused)
   std::vector<float*> dz;    // dz[l] = dZ_l, l = 1..L (dz[L] = dY)
-  std::vector<int64_t> ld;   // ld[l] = round_up(widths[l], 4)
+  std::vector<int64_t> ld;   // ld[l] = round_up(widths[l], 8); a bf16 dY: to whole k tiles
   float* splitws = nullptr;     // split-K partial products (split_need)
   int64_t splitws_elems = 0;
   float* rsws = nullptr;        // split-K partial row sums (bias gradients)

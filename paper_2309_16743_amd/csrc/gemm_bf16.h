@@ -79,7 +79,6 @@ struct GemmBArgs {
   int64_t target_rows_max;     //   clamped to [0, target_rows_max]
   float scale;
   double* loss_partials;
-  long long* step_now;      // MseBf (nullable): device step counter, advanced by the first block
   const uint16_t* mask;     // MaskBf (bf16 activations)
   int64_t ldmask;
   float* rowsum;            // StoreF32 / SplitK with MNMajor A: sum_k A(m, k) (n tile 0)
@@ -325,7 +324,6 @@ struct BEpi {
         double t = s_red[0];
         for (int w = 1; w < NW; ++w) t += s_red[w];
         g.loss_partials[blockIdx.y * gridDim.x + blockIdx.x] = t;
-        if (g.step_now && blockIdx.x == 0) *g.step_now += 1;
       }
       if (g.colsum && (wid & 1) == 0 && rl == 0) {
         for (int c = 0; c < 4; ++c) {

@@ -420,10 +420,13 @@ __global__ __launch_bounds__(256) void splitk_adam_kernel(const float* __restric
 
 namespace ot {
 
-// db[n] = sum over m-tiles t (in order) of colsum[t * ld + n].
+// db[n] = sum over m-tiles t (in order) of colsum[t * ld + n].  The first thread
+// also advances the device step counter (step_now, nullable), which the step's
+// Adam kernels read after this launch.
 __global__ void colsum_reduce_kernel(const float* __restrict__ colsum, int64_t tiles, int64_t N, int64_t ld,
-                                     float* __restrict__ db) {
+                                     float* __restrict__ db, long long* __restrict__ step_now) {
   const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (n == 0 && step_now) *step_now += 1;
   if (n >= N) return;
   float acc = 0.f;
   for (int64_t t = 0; t < tiles; ++t) acc += colsum[t * ld + n];
@@ -563,8 +566,9 @@ struct ot_surrogate {
   bool fused_step = false;    // ... and the current step took that path
   ot::AdamArgs step_adam{};   // Adam scalars of the current step
   // Device step counter (surrogate_set_device_step): steps taken, advanced by
-  // the first block of a step's output forward and read by its Adam kernels,
-  // so that a step's launches can be captured once and replayed.
+  // the first block of a step's output forward (bf16: of the output bias
+  // gradient's reduction after it) and read by its Adam kernels, so that a
+  // step's launches can be captured once and replayed.
   long long* t_now_dev = nullptr;
   bool device_step = false;
   // Workspaces, sized for ws_rows batch rows.
@@ -1053,8 +1057,9 @@ int forward_hidden_bf16(ot_surrogate* s, const float* X, int64_t ldx, int64_t ro
 }
 
 // bf16 forward of b rows and the output layer's fused MSE epilogue: dY (bf16)
-// into dz16[L], per-block loss partials; with bias_grad also the output bias
-// gradient (column sums of the rounded dY) into grads.  *n_partials receives
+// into dz16[L], per-block loss partials; with bias_grad (a train step) also the
+// output bias gradient (column sums of the rounded dY) into grads, and the
+// device step counter advanced.  *n_partials receives
 // the number of loss partials.
 int forward_mse_bf16(ot_surrogate* s, const float* x, int64_t ldx, const float* u, int64_t ldu, const int32_t* u_rows,
                      int64_t u_rows_max, int64_t b, hipStream_t st, bool bias_grad, int64_t* n_partials) {
@@ -1083,7 +1088,6 @@ int forward_mse_bf16(ot_surrogate* s, const float* x, int64_t ldx, const float* 
   g.target_rows_max = u_rows_max;
   g.scale = (float)(2.0 / ((double)b * (double)D));
   g.loss_partials = s->loss_partials;
-  g.step_now = bias_grad && s->device_step ? s->t_now_dev : nullptr;   // a train step, not an evaluation
   if (bias_grad) {
     // output bias gradient: per m-tile column sums of the rounded dY
     g.colsum = s->colsum;
@@ -1098,7 +1102,7 @@ int forward_mse_bf16(ot_surrogate* s, const float* x, int64_t ldx, const float* 
   if (bias_grad) {
     const int64_t used_mtiles = ot::ceil_div(b, ot::tile_rows_b(pf.cfg));
     hipLaunchKernelGGL(ot::colsum_reduce_kernel, dim3((unsigned)ot::ceil_div(D, 256)), dim3(256), 0, st, s->colsum,
-                       used_mtiles, D, s->ld[L], s->grads + lo.b_off);
+                       used_mtiles, D, s->ld[L], s->grads + lo.b_off, s->device_step ? s->t_now_dev : nullptr);
     OT_LAUNCHED("colsum_reduce_kernel");
   }
   return OT_OK;

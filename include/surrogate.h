@@ -93,7 +93,7 @@ int surrogate_set_lr(ot_surrogate* s, float lr);
  * 1 - beta^t (Kingma and Ba's Algorithm 1, the optimizer of Sec. 4.1) depend
  * on the step t, normally a host-side argument of the step's kernels; with
  * enable = 1 the kernels read the number of the step from device memory
- * instead, which the step's output forward advances, so that the captured
+ * instead, which the step itself advances before them, so that the captured
  * launches stay valid for every replay.  The corrections are
  * formed the same way in both modes (binary exponentiation in double), so
  * steps agree bit for bit.  Switching synchronises the device; with the

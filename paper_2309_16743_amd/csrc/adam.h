@@ -28,9 +28,9 @@ __host__ __device__ inline float bias_correction(float beta, long long t) {
 struct AdamArgs {
   float lr, b1, b2, eps;
   float c1, c2;   // bias corrections 1 - b1^t, 1 - b2^t of the step being taken
-  // When set, the step being taken is t = *t_now (device memory, advanced by the
-  // step's output forward) and the kernel forms c1, c2 itself (resolved()), so
-  // that a captured step replays with the same arguments.
+  // When set, the step being taken is t = *t_now (device memory, advanced
+  // earlier in the step) and the kernel forms c1, c2 itself (resolved()), so that
+  // a captured step replays with the same arguments.
   const long long* t_now;
 
 #ifdef __HIPCC__
